@@ -41,8 +41,8 @@ PEAK = {"bf16": 2516.6e12, "f32": 157.3e12}   # dense MFMA, FLOP/s
 PEAK_HBM = 8.0e12         # bytes/s
 N_SIMD = 1024             # 256 CUs x 4 SIMDs
 N_XCD = 8                 # GRBM_GUI_ACTIVE reads as the sum over the 8 XCDs
-# forward kernels: general, pointwise, pipelined pointwise, stride-2 stem
-KERNEL_TAGS = ("bsp::fwd::k_fwd<", "bsp::pw::k_pw<", "bsp::pl::k_pl<", "bsp::stem::k_stem(")
+# forward kernels: 3-wide convs, general, pointwise, pipelined pointwise, stride-2 stem
+KERNEL_TAGS = ("bsp::cv::k_cv<", "bsp::fwd::k_fwd<", "bsp::pw::k_pw<", "bsp::pl::k_pl<", "bsp::stem::k_stem(")
 AUX_TAGS = ("k_im2col", "k_splitk_sum")   # expansion and partial-sum kernels some layers add to a step
 CALIB_BYTES = 256 << 20   # plain copy kernel (torch.neg on bf16) that calibrates the HBM counters
 COLD_BYTES = 512 << 20    # buffer sets rotated through for cold-cache layer times (2x the last-level cache)

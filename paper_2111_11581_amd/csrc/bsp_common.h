@@ -167,6 +167,10 @@ struct Plan {
     int NGR;                      // 16-byte granules per patch row (one channel of a tile)
     int gpg;                      // 4-pixel groups per granule
     int occ;                      // workgroups per CU the plan is sized for
+    // 3-wide bf16 convs (k_cv)
+    int cv;                       // 1: k_cv runs this layer
+    int NT, lg_wp;                // pixel tiles (16) per wave, log2 of the waves along pixels
+    int cv_nch;                   // estimated chunks of the K loop
     // dev_tiles layout (bytes); with a row map, off_rowmap holds int32 rowmap[n_mt_pad * 16]
     // (kept output row of each computed row, 0 past RK) followed by the R - RK pruned rows
     int64_t off_chunks, off_desc, off_desc16, off_a, off_rowmap, off_pruned, off_counts, tile_bytes;
@@ -180,6 +184,9 @@ struct Plan {
 // Returns BSP_OK or an error.
 bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv_or_null, bsp_dtype wdt,
                      int batch_for_linear, Plan *p);
+
+// Modelled time of a tiling of k_cv for a plan (see bsp_plan.cpp).
+double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG, int lg_wp);
 
 // Per-call launch arguments of the forward kernel.
 struct ConvArgs {
@@ -257,6 +264,37 @@ struct PwArgs {
     FastDiv div_kpart;
     int64_t part_stride;
 };
+
+// Launch arguments of the kernel of 3-wide bf16 convs.
+struct CvArgs {
+    const uint16_t *x;
+    void *y;
+    const uint8_t *tiles;
+    const float *bias;
+    const int32_t *rowmap;        // output row of each computed row (row-mapped kernels only)
+    int relu, out_bf16;
+    int Cin, H, W, R, Rout, Ho, Wo, KH, SH, PH, PW;
+    int x_cs;                     // channel stride of x (elements; x holds fewer than 2^31)
+    int64_t x_total;              // elements of x
+    int CC;                       // channels of a chunk's patch
+    int mask_own;                 // some unit's own columns leave the image
+    int64_t y_cs;
+    int GPR, CH_STRIDE, VS;
+    int n_groups, group_rows, mt_per_group, S, MBT, n_mb, lg_wp;
+    int n_groups_total;           // 4-pixel groups over all images
+    int grid_valid;
+    int64_t off_chunks, off_desc16, off_a;
+    uint32_t fp_lo, fp_hi;
+    FastDiv div_GPR, div_Ho, div_nmb;
+};
+constexpr int kCvWaves = 8, kCvThreads = 64 * kCvWaves;
+constexpr int kCvMaxAcc = 16;              // m-tiles x pixel tiles of a wave
+// waves per SIMD: four while the accumulators fit 128 registers with everything else
+BSP_HD constexpr int cv_wps(int tm, int nt) { return tm * nt <= 8 ? 4 : 2; }
+// steps of a chunk: its weights and offsets are held in registers
+BSP_HD constexpr int cv_smax(int tm, int nt) { return cv_wps(tm, nt) == 4 ? 4 / tm : (tm == 4 ? 2 : 4); }
+BSP_HD constexpr int cv_upt(int sw) { return sw == 1 ? 6 : 4; }    // units a thread holds in registers
+constexpr int kCvRound = 62 * kCvWaves;    // units of a workgroup per round (lanes 0 and 63 load for their neighbours)
 
 // Workgroups per CU the pointwise kernel's register budget allows (its launch
 // bound): element size, gather mode (1: stride 1, 2: stride 2), m-tiles per wave.

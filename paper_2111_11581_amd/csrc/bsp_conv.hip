@@ -3,10 +3,17 @@
 // bsp_fwd_*.hip (one translation unit per element type and gather mode).
 #include <mutex>
 
+#include "bsp_cv.h"
 #include "bsp_pl.h"
 #include "bsp_pw.h"
 
 namespace bsp {
+namespace cv {
+
+cv_fn pick_1(int NT, int TM, int TPG, bool map);   // stride 1
+cv_fn pick_2(int NT, int TM, int TPG, bool map);   // stride 2
+
+}  // namespace cv
 namespace pl {
 
 pl_fn pick_1(int NSUB, int TM, bool map);
@@ -326,10 +333,78 @@ static hipError_t launch_pw(const Plan &p, int n, const void *x, const uint8_t *
     return launch_fill_pruned(p, images, a.y_cs, a.y_is, a.y_cs, tiles, bias, relu, out_bf16, y, st);
 }
 
+// 3-wide bf16 convs.
+static hipError_t launch_cv(const Plan &p, int n, const void *x, const uint8_t *tiles, const float *bias, int relu,
+                            int out_bf16, void *y, hipStream_t st) {
+    CvArgs a;
+    memset(&a, 0, sizeof(a));
+    a.x = (const uint16_t *)x;
+    a.y = y;
+    a.tiles = tiles;
+    a.bias = bias;
+    a.rowmap = p.rowmap ? (const int32_t *)(tiles + p.off_rowmap) : nullptr;
+    a.relu = relu;
+    a.out_bf16 = out_bf16;
+    a.Cin = p.Cin; a.H = p.H; a.W = p.W; a.R = p.RK; a.Rout = p.R; a.Ho = p.Ho; a.Wo = p.Wo;
+    a.KH = p.KH; a.SH = p.SH; a.PH = p.PH; a.PW = p.PW;
+    a.x_cs = p.H * p.W;
+    a.x_total = (int64_t)n * p.Cin * p.H * p.W;
+    a.CC = p.CC;
+    a.mask_own = p.W % (4 * p.SW) != 0 || p.PW != 1;
+    a.y_cs = (int64_t)p.Ho * p.Wo;
+    a.GPR = p.GPR; a.CH_STRIDE = p.CH_STRIDE; a.VS = p.VS;
+    a.n_groups = p.n_groups; a.group_rows = p.group_rows; a.mt_per_group = p.mt_per_group;
+    const int64_t groups = (int64_t)n * p.Ho * p.GPR;
+    // Fewer images than the tiling was planned for: smaller tiles (one m-tile per wave) run
+    // on the same packed layout, whose strides hold the planned tile's rows, and spread a
+    // small layer over more CUs.  256 -> 256 at 28x28 -> 14x14, 5 images: 20.4 us with the
+    // planned tiles, 15.6 us with these.
+    int NT = p.NT, TM = p.TM, TPG = p.TPG, lg_wp = p.lg_wp;
+    if (n < kNominalImages) {
+        const int n_mt = p.n_groups * p.mt_per_group;
+        double best = cv_cost(p, groups, n_mt, NT, TM, TPG, lg_wp);
+        for (int nt = 2; nt <= 4; nt *= 2) {
+            if (4 * nt > (4 * p.NT) << p.lg_wp || p.SMAX > cv_smax(1, nt)) continue;
+            const double c = cv_cost(p, groups, n_mt, nt, 1, 1, 0);
+            if (c < best) {
+                best = c;
+                NT = nt; TM = TPG = 1; lg_wp = 0;
+            }
+        }
+    }
+    a.S = p.S; a.lg_wp = lg_wp;
+    a.MBT = TM * (kCvWaves >> lg_wp);
+    a.n_mb = div_up(p.n_groups * p.mt_per_group, a.MBT);
+    const int TG = (4 * NT) << lg_wp;
+    const int64_t gv = div_up64(groups, TG) * a.n_mb;
+    if (groups + TG > INT32_MAX || gv > INT32_MAX - 8) return hipErrorInvalidValue;
+    a.n_groups_total = (int)groups;
+    a.grid_valid = (int)gv;
+    a.off_chunks = p.off_chunks; a.off_desc16 = p.off_desc16; a.off_a = p.off_a;
+    a.fp_lo = (uint32_t)p.fingerprint;
+    a.fp_hi = (uint32_t)(p.fingerprint >> 32);
+    a.div_GPR = make_fastdiv((uint32_t)p.GPR);
+    a.div_Ho = make_fastdiv((uint32_t)p.Ho);
+    a.div_nmb = make_fastdiv((uint32_t)a.n_mb);
+    const cv::cv_fn fn = p.SW == 1 ? cv::pick_1(NT, TM, TPG, p.rowmap != 0) : cv::pick_2(NT, TM, TPG, p.rowmap != 0);
+    if (!fn) return hipErrorInvalidValue;
+    if (p.lds_total > 48 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 p.lds_total);
+        if (e != hipSuccess) return e;
+    }
+    const int grid = (int)(div_up64(gv, 8) * 8);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kCvThreads), (size_t)p.lds_total, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_fill_pruned(p, n, a.y_cs, (int64_t)p.R * a.y_cs, a.y_cs, tiles, bias, relu, out_bf16, y, st);
+}
+
 hipError_t launch_conv(const Plan &p, int n, const void *x, const uint8_t *tiles, const float *bias,
                        int relu, int out_bf16, void *y, hipStream_t st, void *part) {
     if (p.pw) return launch_pw(p, n, x, tiles, bias, relu, out_bf16, y, st, part);
     if (stem_ok(p, x)) return launch_stem(p, n, x, tiles, bias, relu, out_bf16, y, st);
+    if (p.cv) return launch_cv(p, n, x, tiles, bias, relu, out_bf16, y, st);
     ConvArgs a;
     memset(&a, 0, sizeof(a));
     a.x = x;

@@ -10,6 +10,7 @@
 // windows ("chunks") the forward stages through LDS.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <vector>
 
 #include "bsp_kernels.h"
@@ -386,7 +387,7 @@ __global__ void k_step_spans(const int32_t *__restrict__ desc, int n_groups, int
     }
 }
 
-__global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int *n_chunks, int *flag) {
+__global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int lo_max, int *n_chunks, int *flag) {
     extern __shared__ int spans[];  // 2*S
     for (int s = threadIdx.x; s < S; s += blockDim.x) {
         spans[2 * s] = table[s].x;
@@ -396,7 +397,8 @@ __global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int *n_chun
     if (threadIdx.x != 0) return;
     int nc = 0, s = 0;
     while (s < S) {
-        const int lo = spans[2 * s];
+        // k_cv stages CC channels of every chunk: none may start past Cin - CC (lo_max)
+        const int lo = min(spans[2 * s], lo_max);
         int hi = spans[2 * s + 1];
         if (hi - lo + 1 > CC) {
             atomicOr(flag, 2);
@@ -419,7 +421,7 @@ __global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int *n_chun
 // steps); the offset of a kept column relative to the chunk's first channel is
 // below CC * CH_STRIDE, which fits 16 bits by the LDS budget.
 __global__ void k_desc16(const int32_t *__restrict__ desc, const int4 *__restrict__ table,
-                         const int *n_chunks_p, int n_groups, int LP, int CH_STRIDE,
+                         const int *n_chunks_p, int n_groups, int LP, int CH_STRIDE, int cv,
                          uint16_t *__restrict__ desc16, int *flag) {
     const int n = n_groups * LP;
     const int nch = *n_chunks_p;
@@ -431,11 +433,14 @@ __global__ void k_desc16(const int32_t *__restrict__ desc, const int4 *__restric
             if (s >= t.x && s < t.y) { lo = t.z; break; }
         }
         const int off = desc[e] - lo * CH_STRIDE;
+        // k_cv: entries t = 8 kg + 4 h + q of a step at 2 (4 kg + q) + h (a lane's two reads)
+        const int t = e & 31;
+        const int d = cv ? (e & ~31) + 2 * (4 * (t >> 3) + (t & 3)) + ((t >> 2) & 1) : e;
         if (lo < 0 || off < 0 || off > 0xffff) {
             atomicOr(flag, 2);
-            desc16[e] = 0;
+            desc16[d] = 0;
         } else {
-            desc16[e] = (uint16_t)off;
+            desc16[d] = (uint16_t)off;
         }
     }
 }
@@ -661,10 +666,10 @@ bsp_status pack_t(const Plan &p, const E *w, const uint8_t *mask, E *values, int
         int4 *table = (int4 *)(tiles + p.off_chunks);
         k_step_spans<<<grid_for(p.S), 256, 0, st>>>(desc, p.n_groups, p.LP, p.S, p.CH_STRIDE, table);
         k_build_chunks<<<1, 256, sizeof(int) * 2 * p.S, st>>>(
-            table, p.S, p.CC, p.SMAX, (int *)(tiles + offsetof(TileHeader, n_chunks)), flag);
+            table, p.S, p.CC, p.SMAX, p.cv ? p.Cin - p.CC : INT_MAX, (int *)(tiles + offsetof(TileHeader, n_chunks)), flag);
         k_desc16<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
             desc, table, (const int *)(tiles + offsetof(TileHeader, n_chunks)), p.n_groups, p.LP,
-            p.CH_STRIDE, (uint16_t *)(tiles + p.off_desc16), flag);
+            p.CH_STRIDE, p.cv, (uint16_t *)(tiles + p.off_desc16), flag);
     }
     if (p.n_g_pad > p.n_groups) {
         // offsets of the padding groups of the last m-block: 0 (a valid patch position)

@@ -56,7 +56,7 @@ static int max_slots(int TG, int GPR, int Ho, int KH, int SH, int PH) {
 // Padding of the m-tile range, dev_tiles layout and the fingerprint the kernels
 // check against the packed header.
 static void finish_layout(Plan *p, int n_mt, int astep) {
-    p->n_mt_pad = p->n_mb * p->MBT;
+    p->n_mt_pad = p->cv ? round_up(p->n_mb * p->MBT, kCvWaves) : p->n_mb * p->MBT;
     p->n_g_pad = p->shared ? 1 : std::max(p->n_groups, p->n_mb * p->MBG);
     if (p->shared) p->n_mt_pad = std::max(p->n_mt_pad, n_mt);
 
@@ -73,7 +73,7 @@ static void finish_layout(Plan *p, int n_mt, int astep) {
                        p->mt_per_group, p->LP, p->S, p->CH_STRIDE, p->RS, p->LEFT, p->NSLOT,
                        p->CC, p->KH, p->KW, p->is_linear, p->SW, p->NSUB, p->SMAX, p->resident,
                        p->MBT, p->MBG, p->n_mt_pad, p->n_g_pad, p->GE, p->NB, p->pw, p->NGR, p->VS, p->V,
-                       p->rowmap, p->RK, p->khw, (int)p->counts_hash, p->counts != nullptr, p->pl, 13};
+                       p->rowmap, p->RK, p->khw, (int)p->counts_hash, p->counts != nullptr, p->pl, p->cv, 14};
     p->fingerprint = fnv1a(fpv, (int)(sizeof(fpv) / sizeof(fpv[0])));
 }
 
@@ -606,6 +606,101 @@ static double search_tiling(Plan *p, int span_req, double step_ch, int n_mt, int
     return best;
 }
 
+// Cube of the time (CU cycles) of k_cv with tiles of NT x 2^lg_wp pixel tiles and TM m-tiles per wave
+// (lists shared by TPG of them) for `groups` 4-pixel groups and n_mt m-tiles: the larger
+// (3-norm) of what a CU has to issue and of the serial time of its rounds of workgroups.
+// Fitted to 640 measurements on gfx950 (27 layers, 3x3 at stride 1 and 2, planes 2x2 to
+// 56x56, column, row, punched and dense, every tiling): rms error 18%, and the tiling it
+// picks takes 1.04 of the best one's time on average (1.23 at worst).
+double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG, int lg_wp) {
+    const int TG = (4 * NT) << lg_wp, step = std::min(p.SH, p.KH);
+    const double rows = 1.0 + (double)(TG - 1) / p.GPR;
+    const double slots = rows * step + (p.KH - step) * (1.0 + (double)(TG - 1) / ((double)p.Ho * p.GPR));
+    const int MBT = TM * (kCvWaves >> lg_wp);
+    const int64_t n_wg = div_up64(groups, TG) * div_up(n_mt, MBT);
+    const int occ = std::min(cv_wps(TM, NT) / 2, std::max(1, 160 * 1024 / (p.lds_total + 2048)));
+    const double nti = (double)(NT << lg_wp);
+    const double units = (double)p.cv_nch * p.CC * slots * p.GPR;
+    const double work = units * (p.SW == 1 ? 0.82 : 1.68) + MBT * nti * (p.S * (6.9 / TPG + 6.0) + 120.0);
+    const double serial = 6600.0 + p.cv_nch * 2870.0 + 100.0 * p.S * NT * (TM / TPG);
+    const double a = (double)div_up64(n_wg, 256) * work, b = (double)div_up64(n_wg, 256 * occ) * serial;
+    return a * a * a + b * b * b;
+}
+
+// v or more, r mod 32.
+static int pad_to(int v, int r) { return v + ((r - v) % 32 + 32) % 32; }
+
+// Staged input rows of the worst tile of TG groups: as many output rows as one can span,
+// over as many image boundaries.
+static int cv_slots(const Plan &p, int TG) {
+    const int64_t img = (int64_t)p.Ho * p.GPR;
+    const int rows = rows_spanned(TG, p.GPR);
+    const int cross = img % TG == 0 ? 0 : TG % img == 0 ? (int)(TG / img) - 1 : div_up(rows - 1, p.Ho);
+    return (rows - 1 - cross) * std::min(p.SH, p.KH) + cross * p.KH + p.KH;
+}
+
+// Tiling of a 3-wide bf16 conv for k_cv, for the plan's list layout, scored for the
+// nominal batch.  Sets *p to the best tiling and returns true, or false when none fits.
+static bool plan_cv(Plan *p, int span_req, double step_ch, int n_mt, int mpg) {
+    const int GPR = p->GPR;
+    const int64_t groups = (int64_t)kNominalImages * p->Ho * GPR;
+    double best = 1e300;
+    Plan q = *p, bestp = *p;
+    for (int lg_wp = 0; lg_wp <= 3; ++lg_wp)
+        for (int NT = 2; NT <= 8; NT *= 2) {
+            const int TG = (4 * NT) << lg_wp;
+            if (rows_spanned(TG, GPR) > kMaxTileRows) continue;
+            const int nslot = cv_slots(*p, TG);
+            if (nslot > kMaxSlots) continue;
+            const int uc = nslot * GPR;              // units of a channel (worst tile)
+            // Strides of the copies and channels, padded to 160 and 80 bytes mod 256: the kept
+            // columns of a step start in different LDS banks.  Of 144 residue pairs over 16
+            // layers this one was within 1.2% of each layer's best on average (unpadded: 7.7%,
+            // and 37% for a dense 256-channel layer on 14x14 planes, 64.8 -> 47.3 us).
+            const int VS = 4 * pad_to(uc, 20), chs = 4 * pad_to(3 * VS / 4, 10);
+            for (int TM = 1; TM <= 4; TM *= 2) {
+                if (NT * TM > kCvMaxAcc) continue;   // registers
+                int TPG = TM;
+                if (!p->shared)
+                    while (mpg % TPG) TPG /= 2;
+                if (p->rowmap && TPG != TM) continue;
+                const int smax = cv_smax(TM, NT);
+                // one workgroup per CU only where two do not fit
+                for (int occ = cv_wps(TM, NT) / 2; occ >= 1; --occ) {
+                    int64_t cc = (160 * 1024 / occ - 2048) / (2 * chs);
+                    cc = std::min<int64_t>(std::min<int64_t>(cc, p->Cin), 65536 / chs);   // 16-bit offsets
+                    const int64_t reg_cc = (int64_t)cv_upt(p->SW) * kCvRound / uc;        // units held in registers
+                    if (reg_cc >= span_req) cc = std::min(cc, reg_cc);
+                    if (cc < span_req || cc < 1) continue;
+                    // no more channels than SMAX steps span
+                    const int slack = p->shared ? 1 : (int)step_ch + 1;
+                    cc = std::min<int64_t>(cc, std::max<int64_t>(span_req, (int64_t)std::ceil(smax * step_ch) + slack));
+                    const double spc =
+                        std::min<double>(smax, std::max(1.0, ((double)cc - (p->shared ? 1.0 : step_ch)) / step_ch));
+                    q.CC = (int)cc;
+                    q.cv_nch = (int)std::ceil(p->S / spc);
+                    q.lds_total = (int)cc * chs * 2;
+                    const double cyc = cv_cost(q, groups, n_mt, NT, TM, TPG, lg_wp);
+                    if (cyc >= best * (1 - 1e-9)) break;
+                    best = cyc;
+                    q.cv = 1; q.NT = NT; q.lg_wp = lg_wp;
+                    q.TM = TM; q.TPG = TPG; q.MBT = TM * (kCvWaves >> lg_wp);
+                    q.n_mb = div_up(n_mt, q.MBT);
+                    // padded so that any tiling the launcher may choose (8 m-tiles) has its tiles
+                    q.MBG = div_up(round_up(q.n_mb * q.MBT, kCvWaves), mpg * q.n_mb) + 1;
+                    q.NSLOT = nslot; q.V = 3; q.RS = 4 * GPR; q.VS = VS; q.CH_STRIDE = chs;
+                    q.SMAX = smax; q.occ = occ;
+                    q.NSUB = NT; q.LEFT = 0; q.POFF = 0; q.KS = 1;
+                    bestp = q;
+                    break;
+                }
+            }
+        }
+    if (best >= 1e300) return false;
+    *p = bestp;
+    return true;
+}
+
 static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt,
                                  int batch_for_linear, Plan *p, bool im2col_inner);
 
@@ -650,6 +745,13 @@ bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype 
                             s->regularity == BSP_ROWCOL) && !s->counts;
         const int64_t plane = (int64_t)ho * wo;
         const int64_t kcols = (int64_t)conv->cin * conv->kh * conv->kw;
+        // planes of at most 4 pixels stay on the im2col route: its split K loop fills the chip
+        // (512 -> 512 at 2x2, 32 images: 18.0 us, k_cv 18.4 us)
+        const bool cv = wdt == BSP_BF16 && conv->kw == 3 && conv->stride_w <= 2 && conv->pad_w >= 1 && plane > 4;
+        if (cv) {
+            const bsp_status st = make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
+            if (st != BSP_OK || p->cv) return st;
+        }
         if (sub || plane <= kIm2colMaxPixels ||
             (wdt == BSP_BF16 && lists && plane <= kIm2colListPixels && kcols <= 0xffff &&
              (conv->stride_h > 1 || conv->stride_w > 1 ||
@@ -875,6 +977,15 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
         // pipelined kernel with its split K loop took 0.2-0.7 of the general one's time.
         if ((p->esize == 2 && (!p->shared || p->is_linear || p->Cin > 64) && plan_pl(p, n_mt, astep)) ||
             plan_pointwise(p, span_req, n_mt, mpg, astep)) {
+            finish_layout(p, n_mt, astep);
+            return BSP_OK;
+        }
+    }
+    // 3-wide bf16 convs: k_cv
+    if (!p->is_linear && !im2col_inner && p->esize == 2 && p->KW == 3 && p->SW <= 2 && p->PW >= 1) {
+        Plan c = *p;
+        if (plan_cv(&c, span_req, step_ch, n_mt, mpg)) {
+            *p = c;
             finish_layout(p, n_mt, astep);
             return BSP_OK;
         }
