@@ -19,6 +19,7 @@ __all__ = [
     "bsp_linear", "bsp_maxpool2x2", "bsp_status_string", "bsp_version", "bsp_to_bcs",
 ]
 
+_I64x4 = ctypes.c_int64 * 4
 F32, BF16 = 0, 1
 ROW, COL, UNSTRUCTURED, DENSE, PUNCHED, ROWCOL, PATTERN = 0, 1, 2, 3, 4, 5, 6
 
@@ -67,13 +68,14 @@ def lib():
     if not os.path.exists(_LIB_PATH):
         raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2111_11581_amd.build`")
     L = ctypes.CDLL(_LIB_PATH)
-    P, I32, I64, VP = ctypes.POINTER, ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
+    P, I32, VP = ctypes.POINTER, ctypes.c_int32, ctypes.c_void_p
     sch, cs = P(Scheme), P(ConvShape)
-    L.bsp_packed_sizes.argtypes = [sch, cs, I32, P(I64), P(I64), P(I64), P(I64)]
+    L.bsp_packed_sizes.argtypes = [sch, cs, I32, VP, VP, VP, VP]   # int64 results, by address
     L.bsp_prune.argtypes = [sch, I32, VP, VP, VP]
     L.bsp_prune_noalloc.argtypes = [sch, I32, VP, VP, VP]
     L.bsp_pack.argtypes = [sch, I32, VP, VP, VP, VP, VP, VP, cs, VP]
     L.bsp_unpack.argtypes = [sch, I32, VP, VP, VP, VP, VP]
+    L.bsp_to_bcs.argtypes = [sch] + [VP] * 8
     L.bsp_conv2d.argtypes = [sch, cs, I32, I32, VP, VP, VP, I32, VP, VP]
     L.bsp_linear.argtypes = [sch, I32, I32, I32, VP, VP, VP, I32, VP, VP]
     L.bsp_maxpool2x2.argtypes = [I32, I32, I32, I32, I32, VP, VP, VP]
@@ -102,14 +104,30 @@ def _shape(c) -> ConvShape | None:
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = None   # () -> handle of torch's current stream on the current device
+
+
+def _raw_stream_getter():
+    """torch.cuda.current_stream() builds a Stream object (3 us a call); the raw handle is
+    the same value without it (0.3 us), where this torch offers it."""
+    import torch
+    torch.cuda.current_stream()   # initialises the device
+    get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if get is None or dev is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: get(dev())
 
 
 def _stream(stream):
+    global _raw_stream
     if stream is not None:
         return ctypes.c_void_p(int(getattr(stream, "cuda_stream", stream)))
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = _raw_stream_getter()
+    return _raw_stream()
 
 
 def _check(fn: str, st: int):
@@ -137,12 +155,12 @@ def bsp_version() -> int:
 
 def bsp_packed_sizes(scheme, conv, wdt: int):
     """-> (n_values, n_indices, n_rowptr, dev_tile_bytes)."""
-    out = [ctypes.c_int64() for _ in range(4)]
+    out = _I64x4()
     sh = _shape(conv)
+    a = ctypes.addressof(out)
     _check("bsp_packed_sizes", lib().bsp_packed_sizes(
-        ctypes.byref(_scheme(scheme)), ctypes.byref(sh) if sh is not None else None, int(wdt),
-        *[ctypes.byref(o) for o in out]))
-    return tuple(int(o.value) for o in out)
+        ctypes.byref(_scheme(scheme)), ctypes.byref(sh) if sh is not None else None, int(wdt), a, a + 8, a + 16, a + 24))
+    return tuple(out)
 
 
 def _esize(dt: int) -> int:

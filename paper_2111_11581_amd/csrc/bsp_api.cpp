@@ -1,4 +1,4 @@
-// C ABI entry points: argument validation, planning, dispatch.  No state is kept
+// C ABI entry points: argument validation, planning, dispatch.  Only plans are kept
 // between calls; every device buffer belongs to the caller.
 #include <climits>
 

@@ -6,6 +6,8 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "bsp_common.h"
@@ -729,8 +731,8 @@ constexpr int64_t kIm2colListBytes = 24ll << 20;
 // nothing (its subsampling reads 103 MB), so larger planes stay strided.
 constexpr int kSubsampleMaxPixels = 196;
 
-bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt,
-                     int batch_for_linear, Plan *p) {
+static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt,
+                                int batch_for_linear, Plan *p) {
     const bool sub = s && conv && conv->kh == 1 && conv->kw == 1 && conv->stride_h == 2 && conv->stride_w == 2 &&
                      conv->pad_h == 0 && conv->pad_w == 0 && conv->cin > 0 && conv->h > 0 && conv->w > 0 &&
                      wdt == BSP_BF16 && !s->counts &&
@@ -766,6 +768,60 @@ bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype 
         }
     }
     return make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
+}
+
+// A plan is a pure function of the values below (the batch does not enter), so a thread
+// keeps the plans of the layers it called last: kSets x kWays of them (about 90 KB, freed with
+// the thread), the oldest of a set replaced.  Planning takes 5 to 60 us and a forward call
+// through the Python binding plans twice.  Schemes with per-block counts, whose values are
+// an array of the caller's, are planned anew each time.
+namespace {
+struct PlanKey {
+    int v[20];
+};
+struct PlanCache {
+    static constexpr int kSets = 32, kWays = 4;
+    struct Entry {
+        PlanKey key;
+        bool used;
+        Plan plan;
+    };
+    Entry e[kSets][kWays];
+    int next[kSets];
+};
+}  // namespace
+
+bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt, int batch_for_linear, Plan *p) {
+    if (!s || !p || s->counts) return make_plan_new(s, conv, wdt, batch_for_linear, p);
+    PlanKey key;
+    std::memset(&key, 0, sizeof(key));
+    const int v[] = {s->rows, s->cols, s->bh, s->bw, s->regularity, s->rate, s->khw, (int)wdt,
+                     conv ? 2 : batch_for_linear < 0 ? 0 : 1};
+    std::memcpy(key.v, v, sizeof(v));
+    if (conv) {
+        const int g[] = {conv->cin, conv->h, conv->w, conv->kh, conv->kw, conv->stride_h, conv->stride_w, conv->pad_h,
+                         conv->pad_w};
+        std::memcpy(key.v + sizeof(v) / sizeof(v[0]), g, sizeof(g));
+    }
+    static thread_local std::unique_ptr<PlanCache> cache;
+    if (!cache) cache.reset(new (std::nothrow) PlanCache());
+    if (!cache) return make_plan_new(s, conv, wdt, batch_for_linear, p);
+    const uint64_t h = fnv1a(key.v, (int)(sizeof(key.v) / sizeof(key.v[0])));
+    const int set = (int)((h ^ (h >> 32)) % PlanCache::kSets);
+    for (PlanCache::Entry &e : cache->e[set])
+        if (e.used && std::memcmp(&e.key, &key, sizeof(key)) == 0) {
+            *p = e.plan;
+            return BSP_OK;
+        }
+    const bsp_status st = make_plan_new(s, conv, wdt, batch_for_linear, p);
+    if (st == BSP_OK) {
+        PlanCache::Entry &e = cache->e[set][cache->next[set]];
+        cache->next[set] = (cache->next[set] + 1) % PlanCache::kWays;
+        e.key = key;
+        e.plan = *p;
+        e.used = true;
+    }
+    return st;
 }
 
 static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt,
