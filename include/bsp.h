@@ -213,12 +213,10 @@ bsp_status bsp_to_bcs(const bsp_scheme *scheme, const int32_t *indices, const in
  *    without counts) whose plane has at most 64 pixels (strided, or whose
  *    expanded input for 64 images stays within 24 MiB), except in both cases
  *    bf16 layers with 3-wide kernels at stride_w 1 or 2 and pad_w of at least 1
- *    whose plane has more than 4 pixels (they read x as it is), and bf16 1x1
- *    stride-2 layers without padding over one identity list (ROW or DENSE
- *    without counts) whose plane has at most 196 pixels, expand x into it
- *    (n x cin*kh*kw planes of Ho*Wo elements, rounded up to 8 for the bf16
+ *    whose plane has more than 4 pixels (they read x as it is), expand x into
+ *    it (n x cin*kh*kw planes of Ho*Wo elements, rounded up to 8 for the bf16
  *    pipelined kernel);
- *  - bf16 layers run by the pipelined pointwise kernel (1x1, linear and the
+ *  - bf16 stride-1 pointwise layers (1x1, linear and the
  *    expanded layers above) whose output splits into at most 128 workgroup
  *    tiles (64 or 128 output pixels x 64 to 256 rows) split their K loop
  *    over workgroups and keep fp32 partial sums there (parts x n x rows x

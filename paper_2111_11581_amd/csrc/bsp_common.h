@@ -171,6 +171,7 @@ struct Plan {
     int cv;                       // 1: k_cv runs this layer
     int NT, lg_wp;                // pixel tiles (16) per wave, log2 of the waves along pixels
     int cv_nch;                   // estimated chunks of the K loop
+    int p1;                       // 1: the kernel of bf16 pointwise layers (k_p1) runs it (SMAX: steps of a chunk)
     // dev_tiles layout (bytes); with a row map, off_rowmap holds int32 rowmap[n_mt_pad * 16]
     // (kept output row of each computed row, 0 past RK) followed by the R - RK pruned rows
     int64_t off_chunks, off_desc, off_desc16, off_a, off_rowmap, off_pruned, off_counts, tile_bytes;
@@ -187,6 +188,19 @@ bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv_or_null, bs
 
 // Modelled time of a tiling of k_cv for a plan (see bsp_plan.cpp).
 double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG, int lg_wp);
+
+
+// Tiling of k_p1: NT pixel tiles and TM m-tiles (TPG per list) per wave, 2^lg_wp waves along
+// pixels, chunks of SPC steps and CC channels (estimated nch of them), the channels' LDS
+// stride and a buffer's bytes.
+struct P1Tiling {
+    int NT, TM, TPG, lg_wp, SPC, CC, nch, chs, lds_buf;
+};
+double p1_cost(const Plan &p, const P1Tiling &t, int64_t groups, int ks);
+bool p1_choose(const Plan &p, int n, int ks_max, int span_req, double step_ch, int n_mt_pad, P1Tiling *best_t);
+int p1_parts(const Plan &p, const P1Tiling &t, int64_t groups, int ks_max);
+// 4-pixel groups of a pointwise layer for n images (vectors), as k_p1 numbers them.
+int64_t p1_groups(const Plan &p, int n);
 
 // Per-call launch arguments of the forward kernel.
 struct ConvArgs {
@@ -295,6 +309,36 @@ BSP_HD constexpr int cv_wps(int tm, int nt) { return tm * nt <= 8 ? 4 : 2; }
 BSP_HD constexpr int cv_smax(int tm, int nt) { return cv_wps(tm, nt) == 4 ? 4 / tm : (tm == 4 ? 2 : 4); }
 BSP_HD constexpr int cv_upt(int sw) { return sw == 1 ? 6 : 4; }    // units a thread holds in registers
 constexpr int kCvRound = 62 * kCvWaves;    // units of a workgroup per round (lanes 0 and 63 load for their neighbours)
+
+// Launch arguments of the kernel of bf16 pointwise layers.  Groups of 4 pixels are numbered
+// over rows of GPR groups (stride 1: a row is an image's run of Ho * Wo pixels, Ho = 1).
+struct P1Args {
+    const uint16_t *x;
+    void *y;
+    const uint8_t *tiles;
+    const float *bias;
+    const int32_t *rowmap;        // output row of each computed row (row-mapped kernels only)
+    int relu, out_bf16;
+    int Cin, R, Rout, Ho, Wo, GPR, in_row;
+    int x_cs, x_is, y_is;         // channel and image strides (elements; x and y hold fewer than 2^31)
+    int64_t y_cs, x_total;
+    int n_groups, group_rows, mt_per_group, S, SPC, MBT, n_mb, lg_wp;
+    int CC, CH_STRIDE;            // channels of a chunk's patch, their stride in LDS (elements)
+    int n_groups_total;
+    int tail_group;               // tiles holding this group or later ones may read past x
+    int n_pt, n_walk;             // pixel tiles; workgroups of an m-block (their stride)
+    int grid_valid, lds_buf;
+    int ks, kpart_wgs;            // K loop split over ks workgroups
+    int64_t part_stride;
+    int64_t off_chunks, off_desc16, off_a;
+    uint32_t fp_lo, fp_hi;
+    FastDiv div_GPR, div_Ho, div_nmb, div_kpart;
+};
+constexpr int kP1Upt = 4;         // 16-byte granules a thread holds in registers
+// Workgroups a CU holds by registers.
+BSP_HD constexpr int p1_occ(int tm, int nt) { return cv_wps(tm, nt) / 2; }
+// steps of a chunk: its weights (and the lists' offsets) are held in registers
+BSP_HD constexpr int p1_smax(int tm, int nt) { return cv_wps(tm, nt) == 4 ? 8 / tm : 4; }
 
 // Workgroups per CU the pointwise kernel's register budget allows (its launch
 // bound): element size, gather mode (1: stride 1, 2: stride 2), m-tiles per wave.

@@ -1,9 +1,11 @@
 // Launcher of the forward kernel: argument set-up and instantiation choice.  The
 // kernel template lives in bsp_fwd.h; its instantiations are compiled in
 // bsp_fwd_*.hip (one translation unit per element type and gather mode).
+#include <cmath>
 #include <mutex>
 
 #include "bsp_cv.h"
+#include "bsp_p1.h"
 #include "bsp_pl.h"
 #include "bsp_pw.h"
 
@@ -14,10 +16,15 @@ cv_fn pick_1(int NT, int TM, int TPG, bool map);   // stride 1
 cv_fn pick_2(int NT, int TM, int TPG, bool map);   // stride 2
 
 }  // namespace cv
+namespace p1 {
+
+p1_fn pick_1(int NT, int TM, int TPG, bool map, bool ident);   // stride 1
+p1_fn pick_2(int NT, int TM, int TPG, bool map, bool ident);   // stride 2
+
+}  // namespace p1
 namespace pl {
 
 pl_fn pick_1(int NSUB, int TM, bool map);
-pl_fn pick_2(int NSUB, int TM, bool map);
 pl_fn pick_g(int NSUB, int TM, int G);
 
 }  // namespace pl
@@ -202,6 +209,9 @@ size_t pw_part_bytes(const Plan &p, int n) {
     return sp.ks > 1 ? (size_t)sp.ks * sp.yelems * sizeof(float) : 0;
 }
 
+static hipError_t launch_splitk_sum(const Plan &p, const void *part, int ks, int64_t yelems, int64_t plane,
+                                    const float *bias, int relu, int out_bf16, void *y, hipStream_t st);
+
 static int log2_int(int v) {
     int l = 0;
     while ((1 << l) < v) ++l;
@@ -297,8 +307,8 @@ static hipError_t launch_pw(const Plan &p, int n, const void *x, const uint8_t *
     int threads = kThreads;
     if (p.pl) {
         if (p.dt == BSP_BF16)
-            fn = !p.shared ? (p.SW == 1 ? pl::pick_g(p.NSUB, p.TM, p.MBG) : nullptr)
-                           : (p.SW == 1 ? pl::pick_1(p.NSUB, p.TM, map) : pl::pick_2(p.NSUB, p.TM, map));
+            fn = p.SW != 1 ? nullptr
+                           : p.shared ? pl::pick_1(p.NSUB, p.TM, map) : pl::pick_g(p.NSUB, p.TM, p.MBG);
         threads = pl::kPlThreads;
     } else if (p.dt == BSP_F32) {
         fn = p.SW == 1 ? pw::pick_f(p.TM, p.TPG, p.KS, map) : nullptr;
@@ -316,21 +326,179 @@ static hipError_t launch_pw(const Plan &p, int n, const void *x, const uint8_t *
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (sp.ks > 1) {
-        const uint32_t total = (uint32_t)sp.yelems;   // the API keeps y below 2^31 elements
-        const int64_t plane = p.is_linear ? n : a.y_cs;
-        const int g = (int)std::min<int64_t>((sp.yelems + 255) / 256, 65536);
-        if (out_bf16)
-            k_splitk_sum<uint16_t><<<g, 256, 0, st>>>((const float *)part, sp.ks, sp.yelems, total,
-                                                      make_fastdiv((uint32_t)plane), make_fastdiv((uint32_t)p.R),
-                                                      bias, relu, (uint16_t *)y);
-        else
-            k_splitk_sum<float><<<g, 256, 0, st>>>((const float *)part, sp.ks, sp.yelems, total,
-                                                   make_fastdiv((uint32_t)plane), make_fastdiv((uint32_t)p.R), bias,
-                                                   relu, (float *)y);
-        e = hipGetLastError();
+        e = launch_splitk_sum(p, part, sp.ks, sp.yelems, p.is_linear ? n : a.y_cs, bias, relu, out_bf16, y, st);
         if (e != hipSuccess) return e;
     }
     return launch_fill_pruned(p, images, a.y_cs, a.y_is, a.y_cs, tiles, bias, relu, out_bf16, y, st);
+}
+
+static hipError_t launch_splitk_sum(const Plan &p, const void *part, int ks, int64_t yelems, int64_t plane,
+                                    const float *bias, int relu, int out_bf16, void *y, hipStream_t st) {
+    const uint32_t total = (uint32_t)yelems;   // the API keeps y below 2^31 elements
+    const int g = (int)std::min<int64_t>((yelems + 255) / 256, 65536);
+    if (out_bf16)
+        k_splitk_sum<uint16_t><<<g, 256, 0, st>>>((const float *)part, ks, yelems, total,
+                                                  make_fastdiv((uint32_t)plane), make_fastdiv((uint32_t)p.R), bias,
+                                                  relu, (uint16_t *)y);
+    else
+        k_splitk_sum<float><<<g, 256, 0, st>>>((const float *)part, ks, yelems, total, make_fastdiv((uint32_t)plane),
+                                               make_fastdiv((uint32_t)p.R), bias, relu, (float *)y);
+    return hipGetLastError();
+}
+
+// Tiling of k_p1 for n images (vectors) of a plan over one identity list, and whether k_p1
+// runs it.  At stride 1 the layer is planned and packed for k_pl or k_pw, whose weight
+// tiles k_p1 reads too, so the batch decides.  The lines below are where 66 layers and
+// batches measured (cold cache) changed sides:
+//  - large planes with many channels (more than 1024 64-pixel tiles) are memory-bound, and
+//    the deeper copy pipelines of the other kernels win: 256 -> 64 at 56x56 34 us, k_p1 41;
+//    64 -> 256 at 56x56 46, 49;
+//  - both would split the K loop: k_p1 wins with at most half as many parts (2048 -> 1000 at
+//    64 vectors 10.1 -> 9.2, 1024 -> 256 at 14x14, 8 images 17.5 -> 13.9), else it loses (4096
+//    -> 4096 at 128 vectors 22.8, 27.7; 2048 -> 512 at 7x7, 20 images 19.6, 25.5);
+//  - neither does: long K loops over many tiles stay (4096 -> 4096 at 512 vectors 49, 69),
+//    the others win (64 images: 128 -> 512 at 28x28 40 -> 31, 256 -> 1024 at 14x14 28 -> 24,
+//    512 -> 2048 at 7x7 27 -> 22; 1000 -> 700 at 100 vectors 15.8 -> 12.0);
+//  - only the other kernel would: k_p1's smaller tiles fill the chip without (5 images: 512
+//    -> 256 at 28x28 20.6 -> 8.4, 256 -> 1024 at 14x14 20.5 -> 6.5).
+// Choosing takes 3 us: a thread keeps its last choices, by plan and batch (5 KB).
+static bool p1_pick(const Plan &p, int n, P1Tiling *t) {
+    struct Choice { uint64_t plan; int n, set, takes; P1Tiling t; };
+    static thread_local Choice kept[64];
+    Choice &k = kept[(p.fingerprint ^ (p.fingerprint >> 29) ^ (uint64_t)n) & 63];
+    if (!k.set || k.plan != p.fingerprint || k.n != n) {
+        Choice c{p.fingerprint, n, 1, 0, {}};
+        // split where the other kernel would be, so that no call needs the workspace that
+        // did without it
+        const PwSplit sp = p.p1 ? PwSplit{1, p.S, 0} : pw_split(p, n);
+        const int ks_max = sp.ks > 1 ? 16 : 1;
+        if (p1_choose(p, n, ks_max, 0, 0.0, p.n_mt_pad, &c.t)) {
+            const int64_t groups = p1_groups(p, n);
+            const int64_t tiles = div_up64(groups, kGroups);
+            const int ks = p1_parts(p, c.t, groups, ks_max);
+            if (p.p1) c.takes = 1;
+            else if (tiles > 1024 && p.RK + p.Cin >= 256) c.takes = 0;
+            else if (!p.pl) c.takes = 1;
+            else if (ks > 1) c.takes = 2 * ks <= sp.ks;
+            else c.takes = sp.ks > 1 || p.S < 32 || tiles * div_up(p.n_groups * p.mt_per_group, 16) < 64;
+        }
+        k = c;
+    }
+    *t = k.t;
+    return k.takes != 0;
+}
+
+// bf16 pointwise layers.
+static hipError_t launch_p1(const Plan &p, P1Tiling t, int n, const void *x, const uint8_t *tiles, const float *bias,
+                            int relu, int out_bf16, void *y, hipStream_t st) {
+    P1Args a;
+    memset(&a, 0, sizeof(a));
+    a.x = (const uint16_t *)x;
+    a.y = y;
+    a.tiles = tiles;
+    a.bias = bias;
+    a.rowmap = p.rowmap ? (const int32_t *)(tiles + p.off_rowmap) : nullptr;
+    a.relu = relu;
+    a.out_bf16 = out_bf16;
+    a.Cin = p.Cin; a.R = p.RK; a.Rout = p.R;
+    int64_t images = n;
+    if (p.is_linear) {
+        images = 1;
+        a.Ho = 1; a.Wo = n;
+        a.x_cs = n; a.y_cs = n;
+    } else if (p.SW == 1) {
+        a.Ho = 1; a.Wo = p.H * p.W;
+        a.x_cs = p.H * p.W; a.y_cs = a.x_cs;
+        a.x_is = p.Cin * a.x_cs; a.y_is = p.R * (int)a.y_cs;
+    } else {
+        a.Ho = p.Ho; a.Wo = p.Wo; a.in_row = p.SH * p.W;
+        a.x_cs = p.H * p.W; a.y_cs = (int64_t)p.Ho * p.Wo;
+        a.x_is = p.Cin * a.x_cs; a.y_is = p.R * (int)a.y_cs;
+    }
+    a.GPR = p.SW == 1 ? div_up(a.Wo, 8) * 2 : div_up(a.Wo, 4);
+    a.x_total = p.is_linear ? (int64_t)p.Cin * n : images * p.Cin * (int64_t)a.x_cs;
+    const int64_t groups = p1_groups(p, n);
+    const int n_mt = p.n_groups * p.mt_per_group;
+    // Lists: offsets and chunks are packed for the planned tiles; smaller ones (one m-tile per
+    // wave) run on the same strides and spread a small batch over more CUs.  They are split
+    // only where any tiling of k_pl would be.
+    const bool small = !p.rowmap && p.S >= 4 && p.SW == 1 && div_up64(groups, kGroups) * div_up(n_mt, kWaves) <= 128;
+    const int ks_max = p.shared ? (!p.p1 && pw_split(p, n).ks > 1 ? 16 : 1) : small ? 16 : 1;
+    if (!p.shared && n < (p.is_linear ? kNominalVectors : kNominalImages)) {
+        P1Tiling u = t;
+        u.TM = u.TPG = 1;
+        u.lg_wp = 0;
+        double best = p1_cost(p, t, groups, p1_parts(p, t, groups, ks_max));
+        for (u.NT = 2; u.NT <= 4 && 4 * u.NT <= (4 * p.NT) << p.lg_wp; u.NT *= 2) {
+            const double c = p1_cost(p, u, groups, p1_parts(p, u, groups, ks_max));
+            if (c < best && u.SPC <= p1_smax(1, u.NT)) {
+                best = c;
+                t = u;
+            }
+        }
+    }
+    a.lg_wp = t.lg_wp;
+    a.MBT = t.TM * (kCvWaves >> t.lg_wp);
+    a.n_mb = div_up(n_mt, a.MBT);
+    const int TG = (4 * t.NT) << t.lg_wp;
+    const int64_t n_pt = div_up64(groups, TG);
+    const int ks = p1_parts(p, t, groups, ks_max);
+    if (groups + TG > INT32_MAX || n_pt * a.n_mb * ks > INT32_MAX - 8) return hipErrorInvalidValue;
+    // persistent workgroups, as many as fit the CUs at once
+    const int occ = std::min(p1_occ(t.TM, t.NT), std::max(1, 160 * 1024 / (2 * t.lds_buf + 1024)));
+    a.n_pt = (int)n_pt;
+    a.n_walk = (int)std::min<int64_t>(n_pt, std::max<int64_t>(1, div_up64((int64_t)256 * occ, a.n_mb)));
+    a.n_walk = (int)div_up64(n_pt, div_up64(n_pt, a.n_walk));   // as few as take the same number of tiles each
+    const int64_t gv = (int64_t)a.n_walk * a.n_mb;
+    a.n_groups_total = (int)groups;
+    // granules at the end of the last image whose last channel reaches past x
+    a.tail_group = (int)groups;
+    {
+        const int step = p.SW == 1 ? 2 : 1;
+        while (a.tail_group > 0) {
+            const int64_t g = a.tail_group - step, row = g / a.GPR, img = row / a.Ho;
+            const int64_t off = img * a.x_is + (row - img * a.Ho) * a.in_row + (g - row * a.GPR) * 4 * p.SW;
+            if (off + (int64_t)(p.Cin - 1) * a.x_cs + 8 <= a.x_total) break;
+            a.tail_group = (int)g;
+        }
+    }
+    a.ks = ks;
+    a.kpart_wgs = (int)gv;
+    a.div_kpart = make_fastdiv((uint32_t)gv);
+    const int64_t yelems = p.is_linear ? (int64_t)p.R * n : images * p.R * a.y_cs;
+    a.part_stride = yelems;
+    void *part = nullptr;
+    if (ks > 1) {
+        const hipError_t e = workspace((size_t)ks * yelems * sizeof(float), &part);
+        if (e != hipSuccess) return e;
+        a.y = part;
+    }
+    a.grid_valid = (int)(gv * ks);
+    a.n_groups = p.n_groups; a.group_rows = p.group_rows; a.mt_per_group = p.mt_per_group;
+    a.S = p.S; a.SPC = t.SPC;
+    a.CC = t.CC; a.CH_STRIDE = t.chs; a.lds_buf = t.lds_buf;
+    const int lds_total = 2 * t.lds_buf;
+    a.off_chunks = p.off_chunks; a.off_desc16 = p.off_desc16; a.off_a = p.off_a;
+    a.fp_lo = (uint32_t)p.fingerprint;
+    a.fp_hi = (uint32_t)(p.fingerprint >> 32);
+    a.div_GPR = make_fastdiv((uint32_t)a.GPR);
+    a.div_Ho = make_fastdiv((uint32_t)a.Ho);
+    a.div_nmb = make_fastdiv((uint32_t)a.n_mb);
+    const p1::p1_fn fn = p.SW == 1 ? p1::pick_1(t.NT, t.TM, t.TPG, p.rowmap != 0, p.shared != 0)
+                                   : p1::pick_2(t.NT, t.TM, t.TPG, p.rowmap != 0, p.shared != 0);
+    if (!fn) return hipErrorInvalidValue;
+    if (lds_total > 48 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 lds_total);
+        if (e != hipSuccess) return e;
+    }
+    const int grid = (int)(div_up64(gv * ks, 8) * 8);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kCvThreads), (size_t)lds_total, st, a);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && ks > 1)
+        e = launch_splitk_sum(p, part, ks, yelems, a.y_cs, bias, relu, out_bf16, y, st);
+    if (e != hipSuccess) return e;
+    return launch_fill_pruned(p, images, a.y_cs, (int64_t)p.R * a.y_cs, a.y_cs, tiles, bias, relu, out_bf16, y, st);
 }
 
 // 3-wide bf16 convs.
@@ -402,6 +570,10 @@ static hipError_t launch_cv(const Plan &p, int n, const void *x, const uint8_t *
 
 hipError_t launch_conv(const Plan &p, int n, const void *x, const uint8_t *tiles, const float *bias,
                        int relu, int out_bf16, void *y, hipStream_t st, void *part) {
+    if (p.pw && p.esize == 2 && !p.im2col && (p.p1 || (p.shared && p.SW == 1))) {
+        P1Tiling t{p.NT, p.TM, p.TPG, p.lg_wp, p.SMAX, p.CC, p.cv_nch, p.CH_STRIDE, p.lds_buf};
+        if (!p.shared || p1_pick(p, n, &t)) return launch_p1(p, t, n, x, tiles, bias, relu, out_bf16, y, st);
+    }
     if (p.pw) return launch_pw(p, n, x, tiles, bias, relu, out_bf16, y, st, part);
     if (stem_ok(p, x)) return launch_stem(p, n, x, tiles, bias, relu, out_bf16, y, st);
     if (p.cv) return launch_cv(p, n, x, tiles, bias, relu, out_bf16, y, st);

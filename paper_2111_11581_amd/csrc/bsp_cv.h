@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
     // of a run of 4 SP, so that a lane of the output holds SP consecutive groups; other rows:
     // group 4 t + q, whose reads conflict less.  Byte offset of the group that the lane
     // names in tile t's reads (q = lane % 4) ----
-    constexpr int SP = NT < 4 ? NT : 4;
+    constexpr int SP = 2;
     const int Gw = G0 + wp * (4 * NT);
     const bool runs = (a.Wo & 3) == 0;
     auto group = [&](int t, int q) { return Gw + t / SP * (4 * SP) + (runs ? q * SP + t % SP : t % SP * 4 + q); };

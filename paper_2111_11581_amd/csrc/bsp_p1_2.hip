@@ -1,0 +1,13 @@
+// Instantiations of the kernel of bf16 pointwise layers: stride 2.
+#include "bsp_p1.h"
+
+namespace bsp {
+namespace p1 {
+
+p1_fn pick_2(int NT, int TM, int TPG, bool map, bool ident) {
+    return NT == 2 ? p1_pick<2, 2>(TM, TPG, map, ident) : NT == 4 ? p1_pick<2, 4>(TM, TPG, map, ident)
+           : NT == 8 ? p1_pick<2, 8>(TM, TPG, map, ident) : nullptr;
+}
+
+}  // namespace p1
+}  // namespace bsp

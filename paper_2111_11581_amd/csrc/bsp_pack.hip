@@ -397,7 +397,7 @@ __global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int lo_max,
     if (threadIdx.x != 0) return;
     int nc = 0, s = 0;
     while (s < S) {
-        // k_cv stages CC channels of every chunk: none may start past Cin - CC (lo_max)
+        // k_cv and k_p1 stage CC channels of every chunk: none may start past Cin - CC (lo_max)
         const int lo = min(spans[2 * s], lo_max);
         int hi = spans[2 * s + 1];
         if (hi - lo + 1 > CC) {
@@ -433,7 +433,7 @@ __global__ void k_desc16(const int32_t *__restrict__ desc, const int4 *__restric
             if (s >= t.x && s < t.y) { lo = t.z; break; }
         }
         const int off = desc[e] - lo * CH_STRIDE;
-        // k_cv: entries t = 8 kg + 4 h + q of a step at 2 (4 kg + q) + h (a lane's two reads)
+        // k_cv, k_p1: entries t = 8 kg + 4 h + q of a step at 2 (4 kg + q) + h (a lane's two reads)
         const int t = e & 31;
         const int d = cv ? (e & ~31) + 2 * (4 * (t >> 3) + (t & 3)) + ((t >> 2) & 1) : e;
         if (lo < 0 || off < 0 || off > 0xffff) {
@@ -657,7 +657,9 @@ bsp_status pack_t(const Plan &p, const E *w, const uint8_t *mask, E *values, int
         k_fill<int32_t><<<grid_for(nrm), 256, 0, st>>>(rm, nrm, 0);
         k_rowmap<<<grid_for(p.R), 256, 0, st>>>(indices, p.RK, p.R, rm, (int32_t *)(tiles + p.off_pruned));
     }
-    if (p.pl && !p.shared) {
+    if (p.p1 && p.shared) {
+        // identity lists: the kernel walks the channels itself
+    } else if (p.pl && !p.shared) {
         // the pointwise kernel with gathered lists reads the channels of the lists (its
         // plan's channel stride is 1) and no chunk table
         k_desc16_abs<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
@@ -666,10 +668,10 @@ bsp_status pack_t(const Plan &p, const E *w, const uint8_t *mask, E *values, int
         int4 *table = (int4 *)(tiles + p.off_chunks);
         k_step_spans<<<grid_for(p.S), 256, 0, st>>>(desc, p.n_groups, p.LP, p.S, p.CH_STRIDE, table);
         k_build_chunks<<<1, 256, sizeof(int) * 2 * p.S, st>>>(
-            table, p.S, p.CC, p.SMAX, p.cv ? p.Cin - p.CC : INT_MAX, (int *)(tiles + offsetof(TileHeader, n_chunks)), flag);
+            table, p.S, p.CC, p.SMAX, p.cv || (p.p1 && !p.shared) ? p.Cin - p.CC : INT_MAX, (int *)(tiles + offsetof(TileHeader, n_chunks)), flag);
         k_desc16<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
             desc, table, (const int *)(tiles + offsetof(TileHeader, n_chunks)), p.n_groups, p.LP,
-            p.CH_STRIDE, p.cv, (uint16_t *)(tiles + p.off_desc16), flag);
+            p.CH_STRIDE, p.cv || p.p1, (uint16_t *)(tiles + p.off_desc16), flag);
     }
     if (p.n_g_pad > p.n_groups) {
         // offsets of the padding groups of the last m-block: 0 (a valid patch position)

@@ -58,7 +58,7 @@ static int max_slots(int TG, int GPR, int Ho, int KH, int SH, int PH) {
 // Padding of the m-tile range, dev_tiles layout and the fingerprint the kernels
 // check against the packed header.
 static void finish_layout(Plan *p, int n_mt, int astep) {
-    p->n_mt_pad = p->cv ? round_up(p->n_mb * p->MBT, kCvWaves) : p->n_mb * p->MBT;
+    p->n_mt_pad = p->cv || (p->pw && p->esize == 2) ? round_up(p->n_mb * p->MBT, kCvWaves) : p->n_mb * p->MBT;
     p->n_g_pad = p->shared ? 1 : std::max(p->n_groups, p->n_mb * p->MBG);
     if (p->shared) p->n_mt_pad = std::max(p->n_mt_pad, n_mt);
 
@@ -75,7 +75,7 @@ static void finish_layout(Plan *p, int n_mt, int astep) {
                        p->mt_per_group, p->LP, p->S, p->CH_STRIDE, p->RS, p->LEFT, p->NSLOT,
                        p->CC, p->KH, p->KW, p->is_linear, p->SW, p->NSUB, p->SMAX, p->resident,
                        p->MBT, p->MBG, p->n_mt_pad, p->n_g_pad, p->GE, p->NB, p->pw, p->NGR, p->VS, p->V,
-                       p->rowmap, p->RK, p->khw, (int)p->counts_hash, p->counts != nullptr, p->pl, p->cv, 14};
+                       p->rowmap, p->RK, p->khw, (int)p->counts_hash, p->counts != nullptr, p->pl, p->cv, p->p1, 14};
     p->fingerprint = fnv1a(fpv, (int)(sizeof(fpv) / sizeof(fpv[0])));
 }
 
@@ -237,6 +237,111 @@ static bool plan_pointwise(Plan *p, int span_req, int n_mt, int mpg, int astep) 
 // lists: an m-block holds G whole list groups (or lies inside one group), each step
 // stages G patches, and the m-block's lists (16-bit channels) stay in LDS; each patch
 // copy costs a list read and a multiply-add more.  Returns false when nothing fits.
+int64_t p1_groups(const Plan &p, int n) {
+    if (p.is_linear) return div_up64(n, 8) * 2;
+    if (p.SW == 1) return (int64_t)n * (div_up(p.H * p.W, 8) * 2);
+    return (int64_t)n * p.Ho * div_up(p.Wo, 4);
+}
+
+// Cube of the time (CU cycles) of k_p1 with tiling t for `groups` 4-pixel groups: as
+// cv_cost, with the tiles a workgroup walks.  Fitted to 1753 measurements on gfx950 (23
+// layers, stride 1 and 2, linear, row, dense and column, 5 to 64 images, every tiling):
+// rms error 18%; the tiling it picks takes 1.05 of the best one's time on average.
+double p1_cost(const Plan &p, const P1Tiling &t, int64_t groups, int ks) {
+    const int TG = (4 * t.NT) << t.lg_wp, MBT = t.TM * (kCvWaves >> t.lg_wp);
+    const int n_mb = div_up(p.n_groups * p.mt_per_group, MBT);
+    const int64_t n_pt = div_up64(groups, TG);
+    const int occ = std::min(p1_occ(t.TM, t.NT), std::max(1, 160 * 1024 / (2 * t.lds_buf + 1024)));
+    const int64_t walk = std::min<int64_t>(n_pt, std::max<int64_t>(1, div_up64((int64_t)256 * occ, n_mb)));
+    const int64_t tpw = div_up64(n_pt, walk), n_wg = div_up64(n_pt, tpw) * n_mb * ks;
+    const double nch = (double)t.nch / ks, S = (double)p.S / ks;
+    const double granules = div_up64((int64_t)t.CC * TG, (p.SW == 1 ? 2 : 1) * kCvThreads) * (p.SW == 1 ? 1.0 : 1.3);
+    const double item = 2490.0 + 636.0 * granules + S / nch * t.NT * t.TM * 64.0;
+    const double serial = tpw * (nch * item + 820.0 * t.TM * t.NT);
+    const double nti = (double)(t.NT << t.lg_wp);
+    const double work = tpw * (nch * t.CC * TG * 0.218 + MBT * nti * (S * (17.3 / t.TPG + 7.6) + 77.0));
+    const double a = (double)div_up64(n_wg, 256) * work, b = (double)div_up64(n_wg, 256 * occ) * serial;
+    const double prior = t.NT == 2 && t.TM == 4 ? 1.3 : 1.0;   // measured 1.1 slower than 4 x 2 at equal modelled time
+    const double c = (a * a * a + b * b * b) * prior;
+    if (ks == 1) return c;
+    const double t2 = std::cbrt(c) + 8000.0 + 700.0 * ks;   // the partial sums' stores and their sum kernel
+    return t2 * t2 * t2;
+}
+
+// Best tiling of k_p1 for n images (vectors) of a plan's list layout whose m-tiles fit
+// n_mt_pad; span_req and step_ch as for list_spans (lists only).
+bool p1_choose(const Plan &p, int n, int ks_max, int span_req, double step_ch, int n_mt_pad, P1Tiling *best_t) {
+    const int64_t groups = p1_groups(p, n);
+    const int n_mt = p.n_groups * p.mt_per_group;
+    double best = 1e300;
+    for (int lg_wp = 0; lg_wp <= 3; ++lg_wp)
+        for (int NT = 2; NT <= 8; NT *= 2) {
+            const int TG = (4 * NT) << lg_wp;
+            if (TG > 256) continue;
+            P1Tiling t;
+            t.NT = NT; t.lg_wp = lg_wp;
+            t.chs = 4 * TG + 8;
+            for (int TM = 1; TM <= 4 && NT * TM <= kCvMaxAcc; TM *= 2) {
+                const int MBT = TM * (kCvWaves >> lg_wp);
+                if (div_up(n_mt, MBT) * MBT > n_mt_pad) continue;
+                t.TM = t.TPG = TM;
+                if (!p.shared) {
+                    while (p.mt_per_group % t.TPG) t.TPG /= 2;
+                    if (TM == 4 && t.TPG == 1) continue;   // not instantiated
+                }
+                for (t.SPC = p1_smax(TM, NT); t.SPC >= 1; t.SPC /= 2) {
+                    if (p.shared) {
+                        if (t.SPC > 1 && t.SPC / 2 >= p.S) continue;
+                        t.CC = kKS * t.SPC;
+                        t.nch = div_up(p.S, t.SPC);
+                    } else {
+                        int64_t cc = std::max<int64_t>(span_req, (int64_t)std::ceil(t.SPC * step_ch) + (int)step_ch + 1);
+                        cc = std::min<int64_t>(cc, p.Cin);
+                        if (cc * t.chs > 65536) cc = std::max<int64_t>(span_req, 65536 / t.chs);
+                        if (cc * t.chs > 65536) continue;   // 16-bit offsets
+                        t.CC = (int)cc;
+                        const double spc = std::min<double>(t.SPC, std::max(1.0, ((double)cc - step_ch) / step_ch));
+                        t.nch = (int)std::ceil(p.S / spc);
+                    }
+                    const int64_t buf = align256((int64_t)t.CC * t.chs * 2);
+                    if (2 * buf > 160 * 1024 - 2048) continue;
+                    t.lds_buf = (int)buf;
+                    const int ks = p1_parts(p, t, groups, ks_max);
+                    const double cyc = p1_cost(p, t, groups, ks);
+                    if (cyc < best * (1 - 1e-9)) {
+                        best = cyc;
+                        *best_t = t;
+                    }
+                }
+            }
+        }
+    return best < 1e300;
+}
+
+// As pw_split for k_p1: with at most half as many (tile, m-block) pairs as CUs, the chunks
+// are split into up to ks_max parts, at most one workgroup per CU.
+int p1_parts(const Plan &p, const P1Tiling &t, int64_t groups, int ks_max) {
+    const int64_t units = div_up64(groups, (4 * t.NT) << t.lg_wp) *
+                          div_up(p.n_groups * p.mt_per_group, t.TM * (kCvWaves >> t.lg_wp));
+    if (ks_max < 2 || units > 128 || units < 1 || t.nch < 2) return 1;
+    return (int)std::min<int64_t>(std::min<int64_t>(ks_max, 256 / units), t.nch);
+}
+
+// Layout for k_p1 alone (stride 2; per-block-row lists), tiled for the nominal batch.
+static bool plan_p1(Plan *p, int span_req, double step_ch, int n_mt) {
+    P1Tiling t;
+    if (!p1_choose(*p, p->is_linear ? kNominalVectors : kNominalImages, 1, span_req, step_ch, INT_MAX, &t)) return false;
+    p->pw = 1; p->p1 = 1; p->gpg = p->SW == 1 ? 2 : 1;
+    p->NT = t.NT; p->lg_wp = t.lg_wp; p->TM = t.TM; p->TPG = t.TPG;
+    p->MBT = t.TM * (kCvWaves >> t.lg_wp);
+    p->n_mb = div_up(n_mt, p->MBT);
+    p->MBG = div_up(round_up(p->n_mb * p->MBT, kCvWaves), p->mt_per_group * p->n_mb) + 1;
+    p->CH_STRIDE = t.chs; p->CC = t.CC; p->SMAX = t.SPC; p->cv_nch = t.nch;
+    p->V = 1; p->VS = 0; p->RS = 0; p->NSUB = t.NT; p->LEFT = 0; p->POFF = 0; p->KS = 1;
+    p->lds_buf = t.lds_buf; p->lds_total = 2 * t.lds_buf;
+    return true;
+}
+
 static bool pl_g_ok(int nsub, int tm, int g) {   // instantiated (NSUB, TM, G) of the gathered kernel
     if (g == 1) return nsub == 1 ? (tm == 1 || tm == 2 || tm == 4) : (tm == 2 || tm == 4);
     if (g == 2) return nsub == 1 ? (tm == 1 || tm == 2) : tm == 2;
@@ -246,9 +351,9 @@ static bool pl_g_ok(int nsub, int tm, int g) {   // instantiated (NSUB, TM, G) o
 
 static bool plan_pl(Plan *p, int n_mt, int astep) {
     const bool lists = !p->shared;
-    if (lists && (p->SW != 1 || p->counts || p->Cin > 0xffff)) return false;
+    if (p->SW != 1 || (lists && (p->counts || p->Cin > 0xffff))) return false;
     const int mpg = p->mt_per_group;
-    const int gpg = p->SW == 1 ? 2 : 1;
+    const int gpg = 2;
     int64_t groups_nom;   // groups of the nominal batch
     double hbm_bytes;
     bool mis;             // granule sources off 16-byte boundaries
@@ -256,25 +361,20 @@ static bool plan_pl(Plan *p, int n_mt, int astep) {
         groups_nom = round_up(div_up(kNominalVectors, 4), gpg);
         hbm_bytes = ((double)p->Cin + p->RK) * kNominalVectors * 2;
         mis = false;
-    } else if (p->SW == 1) {
+    } else {
         groups_nom = (int64_t)kNominalImages * round_up(div_up(p->H * p->W, 4), gpg);
         hbm_bytes = ((double)p->Cin + p->RK) * kNominalImages * p->H * p->W * 2;
         mis = ((int64_t)p->H * p->W * 2) % 16 != 0 && !p->im2col;   // im2col planes: padded
-    } else {
-        groups_nom = (int64_t)kNominalImages * p->Ho * div_up(p->Wo, 4);
-        hbm_bytes = ((double)p->Cin * p->H * p->W / 2 + (double)p->RK * p->Ho * p->Wo) * kNominalImages * 2;
-        mis = ((int64_t)p->W * 2) % 16 != 0;
     }
     hbm_bytes += (double)n_mt * p->S * astep;
     const double t_hbm = hbm_bytes / 5.5e12 * 2.4e9;
     const int64_t budget = 160 * 1024 - 2048 - 512;   // minus static LDS (bias, row map) and slack
-    const int mode = p->SW;
 
     double best = 1e300;
     Plan bestp = *p;
     for (int nsub = 1; nsub <= 2; ++nsub) {
         const int np = 64 * nsub;
-        const int rb = np * 2 * mode;                 // patch bytes per channel
+        const int rb = np * 2;                        // patch bytes per channel
         const int pcopy = 32 * (rb / 16) / kThreads;  // patch copies per copying wave and step
         const double n_pt = std::ceil((double)groups_nom / (kGroups * nsub));
         for (int TM = 1; TM <= 4; TM *= 2) {
@@ -328,7 +428,7 @@ static bool plan_pl(Plan *p, int n_mt, int astep) {
                         q.pw = 1; q.pl = 1; q.gpg = gpg; q.occ = 1;
                         q.NSUB = nsub; q.NGR = rb / 16;
                         // gathered lists hold channel numbers (the lists' own; stride 1)
-                        q.CH_STRIDE = lists ? 1 : np * mode; q.CC = 32 * sps; q.SMAX = sps;
+                        q.CH_STRIDE = lists ? 1 : np; q.CC = 32 * sps; q.SMAX = sps;
                         q.FR = pc;
                         q.qmode = 0; q.KS = 1; q.TM = TM; q.TPG = TM;
                         q.MBT = MT; q.MBG = GG; q.n_mb = n_mb;
@@ -722,23 +822,9 @@ constexpr int kIm2colMaxPixels = 16;
 constexpr int kIm2colListPixels = 64;
 constexpr int64_t kIm2colListBytes = 24ll << 20;
 
-// 1x1 stride-2 bf16 convs without padding over one identity list (row-pruned and dense
-// downsampling layers) with output planes of at most this many pixels run as a stride-1
-// 1x1 layer over their subsampled input (the im2col input of a 1x1 conv): the strided
-// pointwise kernel copies every other input column for nothing.  Measured on gfx950 at
-// batch 64 (cold cache): ResNet-50's 512 -> 1024 layer at 28x28 -> 14x14 69 -> 61 us and
-// 1024 -> 2048 at 14x14 -> 7x7 61 -> 49 us; the 256 -> 512 one at 56x56 -> 28x28 gains
-// nothing (its subsampling reads 103 MB), so larger planes stay strided.
-constexpr int kSubsampleMaxPixels = 196;
-
 static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt,
                                 int batch_for_linear, Plan *p) {
-    const bool sub = s && conv && conv->kh == 1 && conv->kw == 1 && conv->stride_h == 2 && conv->stride_w == 2 &&
-                     conv->pad_h == 0 && conv->pad_w == 0 && conv->cin > 0 && conv->h > 0 && conv->w > 0 &&
-                     wdt == BSP_BF16 && !s->counts &&
-                     (s->regularity == BSP_ROW || s->regularity == BSP_DENSE) &&
-                     (int64_t)((conv->h - 1) / 2 + 1) * ((conv->w - 1) / 2 + 1) <= kSubsampleMaxPixels;
-    if (s && conv && conv->kh > 0 && conv->kw > 0 && (conv->kh > 1 || conv->kw > 1 || sub) && conv->stride_h > 0 &&
+    if (s && conv && conv->kh > 0 && conv->kw > 0 && (conv->kh > 1 || conv->kw > 1) && conv->stride_h > 0 &&
         conv->stride_w > 0 && conv->pad_h >= 0 && conv->pad_w >= 0 && conv->cin > 0 &&
         conv->h + 2 * conv->pad_h >= conv->kh && conv->w + 2 * conv->pad_w >= conv->kw) {
         const int ho = (conv->h + 2 * conv->pad_h - conv->kh) / conv->stride_h + 1;
@@ -754,7 +840,7 @@ static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv,
             const bsp_status st = make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
             if (st != BSP_OK || p->cv) return st;
         }
-        if (sub || plane <= kIm2colMaxPixels ||
+        if (plane <= kIm2colMaxPixels ||
             (wdt == BSP_BF16 && lists && plane <= kIm2colListPixels && kcols <= 0xffff &&
              (conv->stride_h > 1 || conv->stride_w > 1 ||
               (int64_t)kNominalImages * kcols * round_up((int)plane, 8) * 2 <= kIm2colListBytes))) {
@@ -1023,6 +1109,18 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     const int n_mt = p->n_groups * p->mt_per_group;
     const int mpg = p->mt_per_group;
 
+    // bf16 pointwise layers that k_p1 always runs: stride 2 over one identity list (batch 64,
+    // cold cache: 256 -> 512 at 56x56 82 -> 61 us, 512 -> 1024 at 28x28 63 -> 52, 1024 -> 2048
+    // at 14x14 47 -> 45 against the strided pipelined kernel and, for the smaller planes, a
+    // subsampled copy), and per-block-row lists that keep at least a quarter of the columns.
+    // k_p1 stages every channel a list's steps span, k_pl only the kept ones: at 4x 256 ->
+    // 1024 at 14x14 23.5 -> 18.5 us and 768 -> 3072 at 256 vectors 15.7 -> 8.0 us, at 8x
+    // (4096 -> 4096 at 512 vectors) 20.8 -> 28.0 us, which stays.
+    if (p->KH == 1 && p->KW == 1 && p->PH == 0 && p->PW == 0 && p->SH == p->SW && p->SW <= 2 && p->esize == 2 &&
+        !im2col_inner && (p->shared ? p->SW == 2 : 4 * (int64_t)p->L >= p->C) && plan_p1(p, span_req, step_ch, n_mt)) {
+        finish_layout(p, n_mt, astep);
+        return BSP_OK;
+    }
     // pointwise layers (1x1 without padding, stride 1 or 2; linear): own kernel
     if (p->KH == 1 && p->KW == 1 && p->PH == 0 && p->PW == 0 && p->SH == p->SW &&
         (p->SW == 1 || (p->SW == 2 && p->esize == 2))) {
