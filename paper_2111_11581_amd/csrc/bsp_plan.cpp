@@ -782,7 +782,13 @@ static bool plan_cv(Plan *p, int span_req, double step_ch, int n_mt, int mpg) {
                     q.CC = (int)cc;
                     q.cv_nch = (int)std::ceil(p->S / spc);
                     q.lds_total = (int)cc * chs * 2;
-                    const double cyc = cv_cost(q, groups, n_mt, NT, TM, TPG, lg_wp);
+                    // a few images too, where the chunks' chain is the whole time: they run the
+                    // planned tiles or, on the same chunks, smaller ones
+                    const int64_t few = groups / kNominalImages * 4;
+                    double cs = cv_cost(q, few, n_mt, NT, TM, TPG, lg_wp);
+                    for (int nt = 2; nt <= 4; nt *= 2)
+                        if (4 * nt <= TG && smax <= cv_smax(1, nt)) cs = std::min(cs, cv_cost(q, few, n_mt, nt, 1, 1, 0));
+                    const double cyc = cv_cost(q, groups, n_mt, NT, TM, TPG, lg_wp) * std::sqrt(cs);
                     if (cyc >= best * (1 - 1e-9)) break;
                     best = cyc;
                     q.cv = 1; q.NT = NT; q.lg_wp = lg_wp;
