@@ -42,7 +42,7 @@ PEAK_HBM = 8.0e12         # bytes/s
 N_SIMD = 1024             # 256 CUs x 4 SIMDs
 N_XCD = 8                 # GRBM_GUI_ACTIVE reads as the sum over the 8 XCDs
 # forward kernels: 3-wide convs, general, pointwise, pipelined pointwise, stride-2 stem
-KERNEL_TAGS = ("bsp::cv::k_cv<", "bsp::fwd::k_fwd<", "bsp::pw::k_pw<", "bsp::pl::k_pl<", "bsp::stem::k_stem(")
+KERNEL_TAGS = ("bsp::cv::k_cv<", "bsp::p1::k_p1<", "bsp::fwd::k_fwd<", "bsp::pw::k_pw<", "bsp::pl::k_pl<", "bsp::stem::k_stem(")
 AUX_TAGS = ("k_im2col", "k_splitk_sum")   # expansion and partial-sum kernels some layers add to a step
 CALIB_BYTES = 256 << 20   # plain copy kernel (torch.neg on bf16) that calibrates the HBM counters
 COLD_BYTES = 512 << 20    # buffer sets rotated through for cold-cache layer times (2x the last-level cache)
@@ -244,8 +244,7 @@ def summarize(args):
         conv = [r for r in stats if is_forward(r["Name"])]
         calls = sum(int(r["Calls"]) for r in conv)
         total_ns = sum(float(r["TotalDurationNs"]) for r in conv)
-        lines += ["# Forward kernels (k_stem: conv1; k_fwd: the 3x3 layers; k_pl: 1x1 layers with more than 64 input channels; "
-                  "k_pw: the other 1x1 layers and fc) on the "
+        lines += ["# Forward kernels (k_stem: conv1; k_cv: the 3x3 layers; k_p1, k_pl, k_pw: the 1x1 layers and fc) on the "
                   "ResNet-50 v1.5 layer pass (batch 64, bf16, %d launches per step)" % n_layers, "",
                   "Kernel trace statistics (rocprofv3 --kernel-trace --stats), command:", "",
                   "    " + args.trace_cmd, "",
@@ -611,7 +610,7 @@ def main():
                       indent=1)
 
     roof = {"bound": "hbm",
-            "kernel": "forward kernels k_stem + k_fwd + k_pl + k_pw (all instantiations, %d launches per step; the step time also holds the im2col expansion and split-K sums of the layers that take them)" % len(ops),
+            "kernel": "forward kernels k_stem + k_cv + k_p1 + k_fwd + k_pl + k_pw (all instantiations, %d launches per step; the step time also holds the im2col expansion and split-K sums of the layers that take them)" % len(ops),
             "achieved": round(achieved_gbs, 1), "peak": PEAK_HBM / 1e9, "unit": "GB/s",
             "frac": round(achieved_gbs * 1e9 / PEAK_HBM, 4), "traffic": None,
             "algorithmic_bytes_per_launch": round(b_alg / len(ops)),

@@ -1,5 +1,5 @@
-// Forward kernel of pointwise layers (1x1 convolutions without padding at stride 1 or
-// 2, fully connected layers, and convolutions run over their im2col input; Sec. 4.2:
+// Forward kernel of pointwise layers (1x1 convolutions without padding at stride 1,
+// fully connected layers, and convolutions run over their im2col input; Sec. 4.2:
 // the GEMM form of a 1x1 layer has one column per input channel).  Template;
 // instantiated in bsp_pl_*.hip.
 //
@@ -23,7 +23,7 @@
 //  * waves 0-3 multiply: wave w works on sub-tile w % NSUB and m-tiles
 //    (w / NSUB) * TM .. + TM - 1 (one list group); per step it reads its weights (one
 //    16-byte LDS read per m-tile) and the 8 channels x 4 pixels of its lane of its
-//    group's patch (8-byte reads, 16-byte at stride 2) at compile-time offsets,
+//    group's patch (8-byte reads) at compile-time offsets,
 //    re-packs them with v_perm into the B operands of 4 MFMA 16x16x32 bf16 and
 //    multiplies; steps of a stage are software-pipelined.  At the end of a tile they
 //    add bias, apply ReLU, round to bf16 and store.
@@ -39,8 +39,7 @@ using namespace bsp::fwd;
 
 constexpr int kPlThreads = 512;
 
-// MODE 1: stride 1, a granule holds two 4-pixel groups; MODE 2: stride 2, a granule
-// holds the 8 input pixels of one group (the even ones are used).
+// MODE 1: stride 1, a granule holds two 4-pixel groups.
 // G: list groups of an m-block (0: the identity list).  With G > 1 the m-block's MT
 // m-tiles are G whole groups of MT / G m-tiles; with G = 1 the m-block lies inside one
 // group.  A wave's TM m-tiles always lie in one group.

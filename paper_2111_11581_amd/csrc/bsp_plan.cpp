@@ -816,15 +816,15 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
 // per output row, which for 2x2 and 4x4 planes copies mostly padding, so such layers run
 // as a 1x1 layer over their im2col input (its columns are the GEMM form's columns).
 constexpr int kIm2colMaxPixels = 16;
-// bf16 convs with per-block-row lists and output planes of at most this many pixels
-// also run over their im2col input, with the pipelined gathered-list kernel: each kept
+// bf16 convs with per-block-row lists and output planes of at most this many pixels that
+// k_cv does not take (kernels not 3 wide) also run over their im2col input, with the pipelined gathered-list kernel: each kept
 // column is then one contiguous input row, copied whole, where the general kernel
 // re-gathers and pads every staged row of a small image.  At stride 1 the expanded
-// input of the nominal batch must stay small: measured on gfx950, the 8x8 VGG-16
-// layers (expanded input up to 19 MB) ran 25% faster this way, the 16x16 ones and
-// ResNet-50's stride-1 7x7 and 14x14 layers (33-59 MB, beyond the L2 caches) slower.
-// Strided layers with such planes gain regardless (ResNet-50's 512-channel stride-2
-// layer, 14x14 -> 7x7: 110 -> 86 us), the general kernel's strided gathers being slower.
+// input of the nominal batch must stay small: measured on gfx950 with 3-wide layers on the
+// general kernel, the 8x8 VGG-16 layers (expanded input up to 19 MB) ran 25% faster this
+// way, the 16x16 ones and ResNet-50's stride-1 7x7 and 14x14 layers (33-59 MB, beyond the
+// L2 caches) slower.  Strided layers with such planes gain regardless (512 channels at
+// stride 2, 14x14 -> 7x7: 110 -> 86 us), the general kernel's strided gathers being slower.
 constexpr int kIm2colListPixels = 64;
 constexpr int64_t kIm2colListBytes = 24ll << 20;
 
