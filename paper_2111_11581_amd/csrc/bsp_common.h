@@ -292,6 +292,7 @@ struct CvArgs {
     int64_t x_total;              // elements of x
     int CC;                       // channels of a chunk's patch
     int mask_own;                 // some unit's own columns leave the image
+    int shift;                    // elements before x that unit offsets count from
     int64_t y_cs;
     int GPR, CH_STRIDE, VS;
     int n_groups, group_rows, mt_per_group, S, MBT, n_mb, lg_wp;
@@ -309,6 +310,25 @@ BSP_HD constexpr int cv_wps(int tm, int nt) { return tm * nt <= 8 ? 4 : 2; }
 BSP_HD constexpr int cv_smax(int tm, int nt) { return cv_wps(tm, nt) == 4 ? 4 / tm : (tm == 4 ? 2 : 4); }
 BSP_HD constexpr int cv_upt(int sw) { return sw == 1 ? 6 : 4; }    // units a thread holds in registers
 constexpr int kCvRound = 62 * kCvWaves;    // units of a workgroup per round (lanes 0 and 63 load for their neighbours)
+
+// A unit of k_cv loads NE = 4 SW input columns of one channel and row, from column col0 on:
+// as few as 1 - PW, so its first columns may lie before the row, and the first rows' before x.
+// Offsets count from `shift` elements before x (or a chunk's first channel), so that none is
+// negative; units with no column in the image (all masked) read from the channel's start.
+BSP_HD inline int cv_col0(const CvArgs &a, int oc, int NE) { return oc * NE + 1 - a.PW; }
+BSP_HD inline uint32_t cv_off(const CvArgs &a, int row_start, int c, int col0, int NE) {
+    return col0 > -NE && col0 < a.W ? (uint32_t)(row_start + c * a.x_cs) + (uint32_t)(col0 + a.shift) : (uint32_t)a.shift;
+}
+// First element a fast load of a unit at offset `off` reads, for a chunk from channel c_first.
+BSP_HD inline int64_t cv_first(const CvArgs &a, uint32_t off, int c_first) {
+    return (int64_t)c_first * a.x_cs - a.shift + (int64_t)off;
+}
+// Whether a chunk of a tile with units near the ends of x loads them element by element.
+BSP_HD inline bool cv_safe(const CvArgs &a, int c_first, int NE) {
+    return (int64_t)c_first * a.x_cs < a.shift || (int64_t)(a.Cin - a.CC - c_first) * a.x_cs < NE;
+}
+// The fields of a layer and its batch that the above read.
+void cv_geometry(const Plan &p, int n, CvArgs *a);
 
 // Launch arguments of the kernel of bf16 pointwise layers.  Groups of 4 pixels are numbered
 // over rows of GPR groups (stride 1: a row is an image's run of Ho * Wo pixels, Ho = 1).

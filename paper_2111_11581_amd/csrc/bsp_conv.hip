@@ -513,14 +513,10 @@ static hipError_t launch_cv(const Plan &p, int n, const void *x, const uint8_t *
     a.rowmap = p.rowmap ? (const int32_t *)(tiles + p.off_rowmap) : nullptr;
     a.relu = relu;
     a.out_bf16 = out_bf16;
-    a.Cin = p.Cin; a.H = p.H; a.W = p.W; a.R = p.RK; a.Rout = p.R; a.Ho = p.Ho; a.Wo = p.Wo;
-    a.KH = p.KH; a.SH = p.SH; a.PH = p.PH; a.PW = p.PW;
-    a.x_cs = p.H * p.W;
-    a.x_total = (int64_t)n * p.Cin * p.H * p.W;
-    a.CC = p.CC;
-    a.mask_own = p.W % (4 * p.SW) != 0 || p.PW != 1;
+    cv_geometry(p, n, &a);
+    a.R = p.RK; a.Rout = p.R;
     a.y_cs = (int64_t)p.Ho * p.Wo;
-    a.GPR = p.GPR; a.CH_STRIDE = p.CH_STRIDE; a.VS = p.VS;
+    a.CH_STRIDE = p.CH_STRIDE; a.VS = p.VS;
     a.n_groups = p.n_groups; a.group_rows = p.group_rows; a.mt_per_group = p.mt_per_group;
     const int64_t groups = (int64_t)n * p.Ho * p.GPR;
     // Fewer images than the tiling was planned for: smaller tiles (one m-tile per wave) run

@@ -160,18 +160,18 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
     const float rUC = 1.f / (float)UC;
     unsigned char *patch = lds;
     // A wave handles 62 units per round in lanes 1 .. 62; lanes 0 and 63 load the units
-    // beside them for their neighbours.  unit(i): byte offset of the unit's own input
-    // columns at the chunk's first channel, LDS offset of its copies (-1: not written),
-    // and which of its own columns, and the ones below and above them, lie in the image.
-    auto unit = [&](int i, int &off, int &dst, uint32_t &own, uint32_t &below, uint32_t &above) {
+    // beside them for their neighbours.  unit(i): offset of the unit's own input columns at
+    // the chunk's first channel (cv_off), LDS offset of its copies (-1: not written), and
+    // which of its own columns, and the ones below and above them, lie in the image.
+    auto unit = [&](int i, uint32_t &off, int &dst, uint32_t &own, uint32_t &below, uint32_t &above) {
         const int uu = (i * kCvWaves + wave) * 62 + lane - 1;
         const int u = min(max(uu, 0), n_units - 1);
         const int c = (int)(((float)u + 0.5f) * rUC), r = u - c * UC;
         const int slot = (int)fdiv((uint32_t)r, a.div_GPR), oc = r - slot * a.GPR;
         const int so = s_slot[slot];
-        const int col0 = oc * NE + 1 - a.PW;
+        const int col0 = cv_col0(a, oc, NE);
         const bool live = so != kNone;
-        off = live ? so + col0 + c * a.x_cs : 0;
+        off = live ? cv_off(a, so, c, col0, NE) : (uint32_t)a.shift;
         dst = (c * a.CH_STRIDE + 4 * r) * 2;
         own = 0;
         if (a.mask_own) {   // columns max(0, -col0) .. min(NE, W - col0) - 1 of the unit
@@ -188,11 +188,12 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         if (!mine || !live) dst = -1;
         // reads that would leave x: the tile's first and last chunks (as far as a window may
         // reach across planes) load element by element
-        if (live && (off < 0 || (int64_t)off + (int64_t)(a.Cin - a.CC) * a.x_cs + NE > a.x_total)) s_edge = 1;
+        if (live && (off < (uint32_t)a.shift || cv_first(a, off, a.Cin - a.CC) + NE > a.x_total)) s_edge = 1;
     };
     // the units held in registers: offset, LDS offset, flags (own: NE bits of NPW units per word)
     constexpr int NPW = 32 / NE;
-    int u_off[UPT], u_dst[UPT];
+    uint32_t u_off[UPT];
+    int u_dst[UPT];
     uint32_t f_own[(UPT + NPW - 1) / NPW] = {}, f_below = 0, f_above = 0;
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
@@ -203,11 +204,11 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         f_above |= ab << i;
     }
     Raw<ND> st[UPT];
-    // input of one unit at the chunk's first channel (xc: x at that channel)
-    auto load_fast = [&](const uint16_t *xc, int off) { return *(const Raw<ND> *)((const char *)xc + (uint32_t)off * 2u); };
-    auto load_safe = [&](int c_first, int off) {
+    // input of one unit (xc: `shift` elements before x at the chunk's first channel)
+    auto load_fast = [&](const uint16_t *xc, uint32_t off) { return *(const Raw<ND> *)((const char *)xc + off * 2u); };
+    auto load_safe = [&](int c_first, uint32_t off) {
         Raw<ND> v;
-        const int64_t e = (int64_t)off + (int64_t)c_first * a.x_cs;
+        const int64_t e = cv_first(a, off, c_first);
 #pragma unroll
         for (int d = 0; d < ND; ++d) {
             const uint32_t lo = e + 2 * d >= 0 && e + 2 * d < a.x_total ? a.x[e + 2 * d] : 0;
@@ -246,10 +247,10 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
             put(st[i], u_dst[i], f_own[i / NPW] >> (i % NPW * NE), bit_mask(f_below, i), bit_mask(f_above, i));
         // units past the registers (lists whose steps span many channels)
         for (int i = UPT; i * kCvRound < n_units; ++i) {
-            int off, dst;
-            uint32_t own, be, ab;
+            int dst;
+            uint32_t off, own, be, ab;
             unit(i, off, dst, own, be, ab);
-            const Raw<ND> v = safe ? load_safe(c_first, off) : load_fast(a.x + (int64_t)c_first * a.x_cs, off);
+            const Raw<ND> v = safe ? load_safe(c_first, off) : load_fast(a.x + cv_first(a, 0, c_first), off);
             put(v, dst, own, (uint32_t)-(int)be, (uint32_t)-(int)ab);
         }
     };
@@ -313,12 +314,12 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         bool safe = false;
         if (c < nch) {
             cd = fwd::chunk_at(table, c);
-            safe = edge && (cd.z * a.x_cs < a.PW || (a.Cin - a.CC - cd.z) * a.x_cs < NE);
+            safe = edge && cv_safe(a, cd.z, NE);
             if (safe) {
 #pragma unroll
                 for (int i = 0; i < UPT; ++i) st[i] = load_safe(cd.z, u_off[i]);
             } else {
-                const uint16_t *xc = a.x + (int64_t)cd.z * a.x_cs;
+                const uint16_t *xc = a.x + cv_first(a, 0, cd.z);
 #pragma unroll
                 for (int i = 0; i < UPT; ++i) st[i] = load_fast(xc, u_off[i]);
             }

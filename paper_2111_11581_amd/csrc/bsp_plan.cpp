@@ -741,6 +741,16 @@ static int cv_slots(const Plan &p, int TG) {
     return (rows - 1 - cross) * std::min(p.SH, p.KH) + cross * p.KH + p.KH;
 }
 
+void cv_geometry(const Plan &p, int n, CvArgs *a) {
+    a->Cin = p.Cin; a->H = p.H; a->W = p.W; a->Ho = p.Ho; a->Wo = p.Wo; a->GPR = p.GPR;
+    a->KH = p.KH; a->SH = p.SH; a->PH = p.PH; a->PW = p.PW;
+    a->x_cs = p.H * p.W;
+    a->x_total = (int64_t)n * p.Cin * p.H * p.W;
+    a->CC = p.CC;
+    a->mask_own = p.W % (4 * p.SW) != 0 || p.PW != 1;
+    a->shift = std::min(p.PW, 4 * p.SW) - 1;
+}
+
 // Tiling of a 3-wide bf16 conv for k_cv, for the plan's list layout, scored for the
 // nominal batch.  Sets *p to the best tiling and returns true, or false when none fits.
 static bool plan_cv(Plan *p, int span_req, double step_ch, int n_mt, int mpg) {

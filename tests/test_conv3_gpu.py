@@ -46,6 +46,13 @@ CASES = [
     (3, 64, 10, 14, 96, 3, (1, 1), (1, 1), (32, 32), PUNCHED, 4, True, "bf16"),
     (2, 30, 9, 9, 80, 3, (1, 1), (1, 1), (0, 0), ROW, 4, True, "bf16"),          # kept filters only
     (70, 16, 6, 6, 24, 3, (1, 1), (1, 1), (8, 16), COL, 2, False, "bf16"),       # more images than planned for
+    # columns before the image in many chunks: neither the first nor the last
+    (2, 256, 14, 14, 48, 3, (1, 1), (2, 2), (0, 0), DENSE, 1, True, "bf16"),
+    (2, 256, 9, 11, 40, 3, (1, 1), (1, 3), (16, 32), COL, 2, False, "bf16"),
+    (1, 256, 15, 13, 32, 3, (2, 2), (2, 2), (0, 0), DENSE, 1, False, "f32"),
+    (3, 192, 10, 16, 32, 3, (2, 2), (1, 3), (16, 16), COL, 2, True, "bf16"),
+    (1, 256, 12, 12, 33, 3, (1, 1), (2, 2), (16, 32), PUNCHED, 2, True, "bf16"),
+    (1, 300, 3, 2, 33, 1, (1, 1), (0, 5), (0, 0), DENSE, 1, False, "bf16"),      # units with no column in the image
 ]
 
 
