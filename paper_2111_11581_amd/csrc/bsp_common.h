@@ -293,6 +293,7 @@ struct CvArgs {
     int CC;                       // channels of a chunk's patch
     int mask_own;                 // some unit's own columns leave the image
     int shift;                    // elements before x that unit offsets count from
+    int col_lo, col_hi;           // first columns of a row's first and last units with a column in the image
     int64_t y_cs;
     int GPR, CH_STRIDE, VS;
     int n_groups, group_rows, mt_per_group, S, MBT, n_mb, lg_wp;
@@ -323,9 +324,21 @@ BSP_HD inline uint32_t cv_off(const CvArgs &a, int row_start, int c, int col0, i
 BSP_HD inline int64_t cv_first(const CvArgs &a, uint32_t off, int c_first) {
     return (int64_t)c_first * a.x_cs - a.shift + (int64_t)off;
 }
-// Whether a chunk of a tile with units near the ends of x loads them element by element.
-BSP_HD inline bool cv_safe(const CvArgs &a, int c_first, int NE) {
-    return (int64_t)c_first * a.x_cs < a.shift || (int64_t)(a.Cin - a.CC - c_first) * a.x_cs < NE;
+// Which ends of x a tile (from output row oh0 of image img0 to oh1 of img1) has units near:
+// bit 0, one may start before x in the first channels; bit 1, one may end behind x in the last
+// ones.  From the tile's first and last input rows, so it holds for all its units.
+BSP_HD inline int cv_edge(const CvArgs &a, int img0, int oh0, int img1, int oh1, int NE) {
+    int top = oh0 * a.SH - a.PH, last = oh1 * a.SH - a.PH + a.KH - 1;
+    top = top < 0 ? 0 : top >= a.H ? a.H - 1 : top;
+    last = last < 0 ? 0 : last >= a.H ? a.H - 1 : last;
+    const int64_t end = ((int64_t)img1 * a.Cin + a.Cin - 1) * a.x_cs + last * a.W + (a.col_hi < 0 ? 0 : a.col_hi) + NE;
+    return (img0 == 0 && top * a.W + a.col_lo < 0 ? 1 : 0) | (end > a.x_total ? 2 : 0);
+}
+// Whether such a tile loads a chunk element by element (a unit reaches fewer than NE elements
+// past its last channel's plane).
+BSP_HD inline bool cv_safe(const CvArgs &a, int edge, int c_first, int NE) {
+    return ((edge & 1) && (int64_t)c_first * a.x_cs < a.shift) ||
+           ((edge & 2) && (int64_t)(a.Cin - a.CC - c_first) * a.x_cs < NE);
 }
 // The fields of a layer and its batch that the above read.
 void cv_geometry(const Plan &p, int n, CvArgs *a);

@@ -90,7 +90,6 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
     extern __shared__ __attribute__((aligned(256))) unsigned char lds[];
     __shared__ int s_rowbase[kMaxTileRows];
     __shared__ int s_slot[kMaxSlots];
-    __shared__ int s_edge;
 
     const int per = gridDim.x >> 3;
     const int lid = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -151,7 +150,6 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         }
         s_rowbase[tid] = base;
     }
-    if (tid == 0) s_edge = 0;
     barrier_lds();
     const int UC = used * a.GPR;       // units of a channel
     const int n_units = a.CC * UC;     // units of a chunk (every chunk stages CC channels)
@@ -186,9 +184,6 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
             for (int k = 0; k < 3; ++k) *(uint2 *)(patch + dst + 2 * k * a.VS) = make_uint2(0u, 0u);
         }
         if (!mine || !live) dst = -1;
-        // reads that would leave x: the tile's first and last chunks (as far as a window may
-        // reach across planes) load element by element
-        if (live && (off < (uint32_t)a.shift || cv_first(a, off, a.Cin - a.CC) + NE > a.x_total)) s_edge = 1;
     };
     // the units held in registers: offset, LDS offset, flags (own: NE bits of NPW units per word)
     constexpr int NPW = 32 / NE;
@@ -209,11 +204,17 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
     auto load_safe = [&](int c_first, uint32_t off) {
         Raw<ND> v;
         const int64_t e = cv_first(a, off, c_first);
+        if (e >= 0 && e + NE <= a.x_total) {
+            const Raw<ND> w = *(const Raw<ND> *)(a.x + e);
 #pragma unroll
-        for (int d = 0; d < ND; ++d) {
-            const uint32_t lo = e + 2 * d >= 0 && e + 2 * d < a.x_total ? a.x[e + 2 * d] : 0;
-            const uint32_t hi = e + 2 * d + 1 >= 0 && e + 2 * d + 1 < a.x_total ? a.x[e + 2 * d + 1] : 0;
-            v.d[d] = lo | hi << 16;
+            for (int d = 0; d < ND; ++d) v.d[d] = w.d[d];
+        } else {
+#pragma unroll
+            for (int d = 0; d < ND; ++d) {
+                const uint32_t lo = e + 2 * d >= 0 && e + 2 * d < a.x_total ? a.x[e + 2 * d] : 0;
+                const uint32_t hi = e + 2 * d + 1 >= 0 && e + 2 * d + 1 < a.x_total ? a.x[e + 2 * d + 1] : 0;
+                v.d[d] = lo | hi << 16;
+            }
         }
         return v;
     };
@@ -299,8 +300,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         }
     };
 
-    barrier_lds();   // s_edge
-    const bool edge = uni(s_edge) != 0;
+    const int edge = cv_edge(a, img0, g0 - img0 * a.Ho, img0 + kl, g1 - (img0 + kl) * a.Ho, NE);
     // Pipeline over the chunks: the input of chunk c is loaded while chunk c - 1
     // multiplies, then its weights (waiting for the input leaves them in flight).
     int4 cp = make_int4(0, 0, 0, 0);
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         bool safe = false;
         if (c < nch) {
             cd = fwd::chunk_at(table, c);
-            safe = edge && cv_safe(a, cd.z, NE);
+            safe = cv_safe(a, edge, cd.z, NE);
             if (safe) {
 #pragma unroll
                 for (int i = 0; i < UPT; ++i) st[i] = load_safe(cd.z, u_off[i]);

@@ -748,7 +748,10 @@ void cv_geometry(const Plan &p, int n, CvArgs *a) {
     a->x_total = (int64_t)n * p.Cin * p.H * p.W;
     a->CC = p.CC;
     a->mask_own = p.W % (4 * p.SW) != 0 || p.PW != 1;
-    a->shift = std::min(p.PW, 4 * p.SW) - 1;
+    const int NE = 4 * p.SW;
+    a->shift = std::min(p.PW, NE) - 1;
+    a->col_lo = cv_col0(*a, (p.PW - 1) / NE, NE);
+    a->col_hi = cv_col0(*a, std::min(p.GPR - 1, (p.W + p.PW - 2) / NE), NE);
 }
 
 // Tiling of a 3-wide bf16 conv for k_cv, for the plan's list layout, scored for the

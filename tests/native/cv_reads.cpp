@@ -23,22 +23,31 @@ void check(int cin, int h, int w, int kh, int sh, int sw, int ph, int pw, const 
         CvArgs a;
         memset(&a, 0, sizeof(a));
         cv_geometry(p, n, &a);
-        for (int g = 0; g < n * p.Ho; ++g)       // output rows, as tiles of one row see them
-            for (int r = 0; r < kh; ++r) {
-                const int img = g / p.Ho, ih = (g - img * p.Ho) * sh - ph + r;
-                if (ih < 0 || ih >= h) continue;
-                const int row = img * cin * a.x_cs + ih * w;
-                for (int oc = 0; oc < p.GPR; ++oc)
-                    for (int ch = 0; ch < p.CC; ch = ch + 1 < p.CC ? p.CC - 1 : p.CC) {
-                        const uint32_t off = cv_off(a, row, ch, cv_col0(a, oc, NE), NE);
-                        for (int cf = 0; cf <= cin - p.CC; ++cf) {
-                            if (cv_safe(a, cf, NE)) continue;
-                            const int64_t at = 2 * cv_first(a, 0, cf) + (uint32_t)(off * 2u);   // bytes
-                            if (at >= 0 && at == 2 * cv_first(a, off, cf)) continue;
-                            if (bad++ < 10)
-                                printf("cin %d %dx%d kh %d s %d,%d p %d,%d n %d: row %d group %d channel %d + %d: byte %lld\n",
-                                       cin, h, w, kh, sh, sw, ph, pw, n, g, oc, cf, ch, (long long)at);
-                        }
+        const int groups = n * p.Ho * p.GPR;
+        for (int TG : {8, 16, (4 * p.NT) << p.lg_wp})   // the tiles the launcher may choose
+            for (int G0 = 0; G0 < groups; G0 += TG) {
+                const int g0 = G0 / p.GPR, g1 = (std::min(G0 + TG, groups) - 1) / p.GPR;
+                const int img0 = g0 / p.Ho, img1 = g1 / p.Ho;
+                const int edge = cv_edge(a, img0, g0 - img0 * p.Ho, img1, g1 - img1 * p.Ho, NE);
+                for (int g = g0; g <= g1; ++g)
+                    for (int r = 0; r < kh; ++r) {
+                        const int img = g / p.Ho, ih = (g - img * p.Ho) * sh - ph + r;
+                        const bool live = ih >= 0 && ih < h;
+                        const int row = img * cin * a.x_cs + ih * w;
+                        for (int oc = 0; oc < p.GPR; ++oc)
+                            for (int ch = 0; ch < p.CC; ch = ch + 1 < p.CC ? p.CC - 1 : p.CC) {
+                                const uint32_t off =
+                                    live ? cv_off(a, row, ch, cv_col0(a, oc, NE), NE) : (uint32_t)a.shift;
+                                // a read moves with the chunk, so the ends of the range decide
+                                for (int cf = 0; cf <= cin - p.CC; cf = cf + 9 < cin - p.CC && cf > 8 ? cin - p.CC - 8 : cf + 1) {
+                                    if (cv_safe(a, edge, cf, NE)) continue;
+                                    const int64_t at = 2 * cv_first(a, 0, cf) + (uint32_t)(off * 2u);   // bytes
+                                    if (at >= 0 && at + 2 * NE <= 2 * a.x_total && at == 2 * cv_first(a, off, cf)) continue;
+                                    if (bad++ < 10)
+                                        printf("cin %d %dx%d kh %d s %d p %d,%d n %d: row %d group %d channel %d + %d: byte %lld\n",
+                                               cin, h, w, kh, sw, ph, pw, n, g, oc, cf, ch, (long long)at);
+                                }
+                            }
                     }
             }
     }
@@ -52,9 +61,9 @@ int main() {
             for (int w : {1, hw, hw + 3})
                 for (int kh : {1, 3})
                     for (int sw : {1, 2})
-                        for (int pw : {1, 2, 3, 5, 12})
+                        for (int pw : {1, 2, 3, 5, 12, 40})
                             for (int bw : {16, 0}) {
-                                const int ph = pw / 2;
+                                const int ph = pw > 12 ? 12 : pw / 2;
                                 if (w + 2 * pw < 3 || hw + 2 * ph < kh) continue;
                                 bsp_scheme s;
                                 memset(&s, 0, sizeof(s));
