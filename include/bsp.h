@@ -168,8 +168,10 @@ bsp_status bsp_prune_noalloc(const bsp_scheme *scheme, bsp_dtype wdt, const void
  *     bsp_linear time; a mismatch is detected on the device and the output
  *     is filled with NaN.
  * Returns BSP_EUNSUPPORTED when one 32-wide step of a kept-column list spans
- * more input channels than one LDS stage holds (only possible for very
- * sparse whole-width column blocks of 1x1 convs). */
+ * more input channels than one LDS stage holds (only possible for whole-width
+ * column blocks, and counted blocks of one block column, in fp32 layers,
+ * kernels larger than 1x1 that are not 3 wide, 1x1 convs at stride 2 and
+ * layers with counts). */
 bsp_status bsp_pack(const bsp_scheme *scheme, bsp_dtype wdt, const void *w, const uint8_t *mask,
                     void *values, int32_t *indices, int32_t *rowptr, void *dev_tiles,
                     const bsp_conv_shape *conv_or_null, void *stream);

@@ -237,6 +237,30 @@ static bool plan_pointwise(Plan *p, int span_req, int n_mt, int mpg, int astep) 
 // lists: an m-block holds G whole list groups (or lies inside one group), each step
 // stages G patches, and the m-block's lists (16-bit channels) stay in LDS; each patch
 // copy costs a list read and a multiply-add more.  Returns false when nothing fits.
+// The layout of a plan's lists as one identity list, pruned weights zero in the tiles.
+static Plan zero_expanded(const Plan &p) {
+    Plan d = p;
+    d.shared = 1;
+    d.L = p.C;
+    d.n_groups = 1;
+    d.group_rows = p.R;
+    d.mt_per_group = div_up(p.R, kMT);
+    d.LP = div_up(d.L, kKS) * kKS;
+    d.S = d.LP / kKS;
+    return d;
+}
+
+// Whether list_spans bounds every step (whole-width blocks, and counted ones of one block
+// column, keep any columns: there it only estimates).  k_cv and k_p1 size a chunk's window by
+// what the steps need; without a bound they take lists only in a window that is the whole
+// input, so that they refuse no mask, and only where that costs no units past the registers
+// and at most twice the modelled time of the estimated window (k_cv: 64 at 28x28, 4x, 23 us on
+// the general kernel, 43 with them), and no workgroup per CU (k_p1: 512 -> 256 at 28x28, 4x,
+// 29.5 on k_pl, 37).  Then it measured up to 2.6 times faster than the kernels that run the rest.
+static bool spans_bounded(const Plan &p) {
+    return p.shared || p.nbc > 1 || (p.reg == BSP_PUNCHED && !p.counts);
+}
+
 int64_t p1_groups(const Plan &p, int n) {
     if (p.is_linear) return div_up64(n, 8) * 2;
     if (p.SW == 1) return (int64_t)n * (div_up(p.H * p.W, 8) * 2);
@@ -305,6 +329,7 @@ bool p1_choose(const Plan &p, int n, int ks_max, int span_req, double step_ch, i
                     }
                     const int64_t buf = align256((int64_t)t.CC * t.chs * 2);
                     if (2 * buf > 160 * 1024 - 2048) continue;
+                    if (!spans_bounded(p) && 4 * buf > 160 * 1024 - 2048) continue;
                     t.lds_buf = (int)buf;
                     const int ks = p1_parts(p, t, groups, ks_max);
                     const double cyc = p1_cost(p, t, groups, ks);
@@ -756,7 +781,8 @@ void cv_geometry(const Plan &p, int n, CvArgs *a) {
 
 // Tiling of a 3-wide bf16 conv for k_cv, for the plan's list layout, scored for the
 // nominal batch.  Sets *p to the best tiling and returns true, or false when none fits.
-static bool plan_cv(Plan *p, int span_req, double step_ch, int n_mt, int mpg) {
+// in_regs: only tilings whose units all fit the registers.
+static bool plan_cv(Plan *p, int span_req, double step_ch, int n_mt, int mpg, bool in_regs) {
     const int GPR = p->GPR;
     const int64_t groups = (int64_t)kNominalImages * p->Ho * GPR;
     double best = 1e300;
@@ -786,6 +812,7 @@ static bool plan_cv(Plan *p, int span_req, double step_ch, int n_mt, int mpg) {
                     cc = std::min<int64_t>(std::min<int64_t>(cc, p->Cin), 65536 / chs);   // 16-bit offsets
                     const int64_t reg_cc = (int64_t)cv_upt(p->SW) * kCvRound / uc;        // units held in registers
                     if (reg_cc >= span_req) cc = std::min(cc, reg_cc);
+                    else if (in_regs) continue;
                     if (cc < span_req || cc < 1) continue;
                     // no more channels than SMAX steps span
                     const int slack = p->shared ? 1 : (int)step_ch + 1;
@@ -855,14 +882,17 @@ static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv,
         // planes of at most 4 pixels stay on the im2col route: its split K loop fills the chip
         // (512 -> 512 at 2x2, 32 images: 18.0 us, k_cv 18.4 us)
         const bool cv = wdt == BSP_BF16 && conv->kw == 3 && conv->stride_w <= 2 && conv->pad_w >= 1 && plane > 4;
-        if (cv) {
-            const bsp_status st = make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
-            if (st != BSP_OK || p->cv) return st;
-        }
-        if (plane <= kIm2colMaxPixels ||
+        const bool expand =
+            plane <= kIm2colMaxPixels ||
             (wdt == BSP_BF16 && lists && plane <= kIm2colListPixels && kcols <= 0xffff &&
              (conv->stride_h > 1 || conv->stride_w > 1 ||
-              (int64_t)kNominalImages * kcols * round_up((int)plane, 8) * 2 <= kIm2colListBytes))) {
+              (int64_t)kNominalImages * kcols * round_up((int)plane, 8) * 2 <= kIm2colListBytes));
+        if (cv) {
+            const bsp_status st = make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
+            // else as a layer that is not 3 wide; so too lists that k_cv would store with zeros
+            if (st == BSP_OK && p->cv && !(expand && lists && p->shared)) return st;
+        }
+        if (expand) {
             if ((int64_t)conv->cin * conv->kh * conv->kw != s->cols) return BSP_EINVAL;
             if (s->regularity == BSP_PUNCHED && conv->kh * conv->kw != s->khw) return BSP_EINVAL;
             const bsp_conv_shape c2 = {conv->n, conv->cin * conv->kh * conv->kw, ho, wo, 1, 1, 1, 1, 0, 0};
@@ -1124,6 +1154,8 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     double step_ch;
     list_spans(*p, &span_req, &step_ch);
 
+    const int window_req = spans_bounded(*p) ? span_req : p->Cin;
+
     const int astep = 64 * 8 * p->esize;   // weight bytes of one m-tile and step
     const int n_mt = p->n_groups * p->mt_per_group;
     const int mpg = p->mt_per_group;
@@ -1136,7 +1168,8 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     // 1024 at 14x14 23.5 -> 18.5 us and 768 -> 3072 at 256 vectors 15.7 -> 8.0 us, at 8x
     // (4096 -> 4096 at 512 vectors) 20.8 -> 28.0 us, which stays.
     if (p->KH == 1 && p->KW == 1 && p->PH == 0 && p->PW == 0 && p->SH == p->SW && p->SW <= 2 && p->esize == 2 &&
-        !im2col_inner && (p->shared ? p->SW == 2 : 4 * (int64_t)p->L >= p->C) && plan_p1(p, span_req, step_ch, n_mt)) {
+        !im2col_inner && (p->shared ? p->SW == 2 : 4 * (int64_t)p->L >= p->C) &&
+        plan_p1(p, window_req, step_ch, n_mt)) {
         finish_layout(p, n_mt, astep);
         return BSP_OK;
     }
@@ -1156,11 +1189,30 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     }
     // 3-wide bf16 convs: k_cv
     if (!p->is_linear && !im2col_inner && p->esize == 2 && p->KW == 3 && p->SW <= 2 && p->PW >= 1) {
-        Plan c = *p;
-        if (plan_cv(&c, span_req, step_ch, n_mt, mpg)) {
+        Plan c = *p, t = *p;
+        const bool bounded = spans_bounded(*p);
+        auto time = [&](const Plan &q) {   // cubed
+            return cv_cost(q, (int64_t)kNominalImages * q.Ho * q.GPR, n_mt, q.NT, q.TM, q.TPG, q.lg_wp);
+        };
+        if (plan_cv(&c, window_req, step_ch, n_mt, mpg, !bounded) &&
+            (bounded || (plan_cv(&t, span_req, step_ch, n_mt, mpg, false) && time(c) <= 8 * time(t)))) {
             *p = c;
             finish_layout(p, n_mt, astep);
             return BSP_OK;
+        }
+        // lists without a bound that do not fit so: stored with zeros (64 images, 16-row blocks, 4x:
+        // 256 at 28x28 246 us on the general kernel's lists, which refuse some masks, 110 so; 256 at
+        // 14x14 49 and 48, at 8x 38 and 48; 64 at 56x56 54 and 44)
+        if (!bounded && !p->counts) {
+            Plan d = zero_expanded(*p);
+            int sr;
+            double sc;
+            list_spans(d, &sr, &sc);
+            if (plan_cv(&d, sr, sc, d.mt_per_group, d.mt_per_group, false)) {
+                *p = d;
+                finish_layout(p, d.mt_per_group, astep);
+                return BSP_OK;
+            }
         }
     }
     // The forward layout.  Per-block-row lists (column, block-punched and row-and-column
@@ -1186,14 +1238,7 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
                               (double)kMT / p->bh_eff * ((double)p->L / p->C) >= 0.2;
     double best = search(&lists);
     if (alt) {
-        Plan d = *p;
-        d.shared = 1;
-        d.L = p->C;
-        d.n_groups = 1;
-        d.group_rows = p->R;
-        d.mt_per_group = div_up(p->R, kMT);
-        d.LP = div_up(d.L, kKS) * kKS;
-        d.S = d.LP / kKS;
+        Plan d = zero_expanded(*p);
         const double bd = search(&d);
         if (bd < (padded_dense ? 1.34 : 0.7) * best) {
             lists = d;
