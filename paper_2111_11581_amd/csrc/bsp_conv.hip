@@ -361,19 +361,21 @@ static hipError_t launch_splitk_sum(const Plan &p, const void *part, int ks, int
 //    512 -> 2048 at 7x7 27 -> 22; 1000 -> 700 at 100 vectors 15.8 -> 12.0);
 //  - only the other kernel would: k_p1's smaller tiles fill the chip without (5 images: 512
 //    -> 256 at 28x28 20.6 -> 8.4, 256 -> 1024 at 14x14 20.5 -> 6.5).
-// Choosing takes 3 us: a thread keeps its last choices, by plan and batch (5 KB).
+// Choosing takes 3 us: a thread keeps its last choices (5 KB), by plan and by the number of
+// pixel groups, through which alone the batch and the plane (no part of the plan's
+// fingerprint) enter.
 static bool p1_pick(const Plan &p, int n, P1Tiling *t) {
-    struct Choice { uint64_t plan; int n, set, takes; P1Tiling t; };
+    struct Choice { uint64_t plan; int64_t groups; int set, takes; P1Tiling t; };
     static thread_local Choice kept[64];
-    Choice &k = kept[(p.fingerprint ^ (p.fingerprint >> 29) ^ (uint64_t)n) & 63];
-    if (!k.set || k.plan != p.fingerprint || k.n != n) {
-        Choice c{p.fingerprint, n, 1, 0, {}};
+    const int64_t groups = p1_groups(p, n);
+    Choice &k = kept[(p.fingerprint ^ (p.fingerprint >> 29) ^ (uint64_t)(groups ^ (groups >> 7))) & 63];
+    if (!k.set || k.plan != p.fingerprint || k.groups != groups) {
+        Choice c{p.fingerprint, groups, 1, 0, {}};
         // split where the other kernel would be, so that no call needs the workspace that
         // did without it
         const PwSplit sp = p.p1 ? PwSplit{1, p.S, 0} : pw_split(p, n);
         const int ks_max = sp.ks > 1 ? 16 : 1;
         if (p1_choose(p, n, ks_max, 0, 0.0, p.n_mt_pad, &c.t)) {
-            const int64_t groups = p1_groups(p, n);
             const int64_t tiles = div_up64(groups, kGroups);
             const int ks = p1_parts(p, c.t, groups, ks_max);
             if (p.p1) c.takes = 1;

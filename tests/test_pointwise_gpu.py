@@ -109,3 +109,38 @@ def test_pointwise_linear_matches_oracle(B, i):
     torch.cuda.synchronize()
     assert torch.all(buf[-64:] == 7.0)
     gate_linear(out_to_f64(from_dev(y, out_dt), out_dt), d["x"], d["w"], m, "bf16", out_dt, bias=d.get("bias"), relu=br)
+
+
+@pytest.mark.parametrize("sizes", [(24, 18), (20, 24)])
+def test_a_layer_runs_as_in_a_thread_of_its_own(B, sizes):
+    """Planes that share packed tiles (nothing in them depends on the size), called in either
+    order: every output has the bits of a thread that called nothing before."""
+    import threading
+
+    import torch
+    from paper_2111_11581_amd.layers import PackedLayer
+    cin, cout, n = 512, 128, 4
+    w = to_dev(draw_layer(ConvLayer("w", n, cin, 8, 8, cout, 1, 1, 1, 1, 0, 0, 0, 0, DENSE, 1, "bf16", ("normal", 0, 1.0),
+                                    ("normal", 0, 0.06)), 10, 200)["w"].reshape(cout, -1), "bf16")
+    x = {s: torch.randn(n, cin, s, s, device="cuda").to(torch.bfloat16) for s in sizes}
+    layers = {s: PackedLayer(B.Scheme(cout, cin, 0, 0, DENSE, 1, 1), B.BF16, w, conv=B.ConvShape(n, cin, s, s, 1, 1, 1, 1, 0, 0))
+              for s in sizes}
+
+    def outputs(order):
+        out = {}
+
+        def call():
+            for s in order:
+                y = torch.empty(n, cout, s, s, device="cuda")
+                layers[s].conv2d(x[s], y, n, B.F32)
+                torch.cuda.synchronize()
+                out[s] = y
+        t = threading.Thread(target=call)
+        t.start()
+        t.join()
+        return out
+
+    alone = {s: outputs([s])[s] for s in sizes}
+    for order in (sizes, sizes[::-1], sizes + sizes):
+        for s, y in outputs(order).items():
+            assert torch.equal(y, alone[s]), (order, s)
