@@ -172,6 +172,7 @@ struct Plan {
     int NT, lg_wp;                // pixel tiles (16) per wave, log2 of the waves along pixels
     int cv_nch;                   // estimated chunks of the K loop
     int p1;                       // 1: the kernel of bf16 pointwise layers (k_p1) runs it (SMAX: steps of a chunk)
+    int p1_split;                 // 1: lists that k_p1 may split the K loop of
     // dev_tiles layout (bytes); with a row map, off_rowmap holds int32 rowmap[n_mt_pad * 16]
     // (kept output row of each computed row, 0 past RK) followed by the R - RK pruned rows
     int64_t off_chunks, off_desc, off_desc16, off_a, off_rowmap, off_pruned, off_counts, tile_bytes;

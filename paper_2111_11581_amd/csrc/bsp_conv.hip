@@ -423,8 +423,8 @@ static hipError_t launch_p1(const Plan &p, P1Tiling t, int n, const void *x, con
     const int n_mt = p.n_groups * p.mt_per_group;
     // Lists: offsets and chunks are packed for the planned tiles; smaller ones (one m-tile per
     // wave) run on the same strides and spread a small batch over more CUs.  They are split
-    // only where any tiling of k_pl would be.
-    const bool small = !p.rowmap && p.S >= 4 && p.SW == 1 && div_up64(groups, kGroups) * div_up(n_mt, kWaves) <= 128;
+    // only where any tiling of k_pl would be, so that no other call needs the workspace.
+    const bool small = p.p1_split && p.S >= 4 && div_up64(groups, kGroups) * div_up(n_mt, kWaves) <= 128;
     const int ks_max = p.shared ? (!p.p1 && pw_split(p, n).ks > 1 ? 16 : 1) : small ? 16 : 1;
     if (!p.shared && n < (p.is_linear ? kNominalVectors : kNominalImages)) {
         P1Tiling u = t;

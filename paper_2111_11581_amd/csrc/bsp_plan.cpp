@@ -1170,6 +1170,8 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     if (p->KH == 1 && p->KW == 1 && p->PH == 0 && p->PW == 0 && p->SH == p->SW && p->SW <= 2 && p->esize == 2 &&
         !im2col_inner && (p->shared ? p->SW == 2 : 4 * (int64_t)p->L >= p->C) &&
         plan_p1(p, window_req, step_ch, n_mt)) {
+        Plan q = *p;
+        p->p1_split = !p->shared && plan_pl(&q, n_mt, astep);   // lists that the gathered kernel takes
         finish_layout(p, n_mt, astep);
         return BSP_OK;
     }

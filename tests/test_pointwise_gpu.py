@@ -144,3 +144,46 @@ def test_a_layer_runs_as_in_a_thread_of_its_own(B, sizes):
     for order in (sizes, sizes[::-1], sizes + sizes):
         for s, y in outputs(order).items():
             assert torch.equal(y, alone[s]), (order, s)
+
+
+# regularity, (bh, bw), counts: lists that the gathered kernel, which splits K loops, does not take
+NO_WORKSPACE = [(COL, (32, 32), True), (COL, (48, 32), False), (ROWCOL, (48, 16), False)]
+
+
+def _captured(i):
+    """In a process of its own: the first forward of a layer is captured into a graph, which a
+    call that allocates the workspace cannot be, and replayed."""
+    import torch
+    import paper_2111_11581_amd as B
+    from paper_2111_11581_amd.layers import PackedLayer
+    reg, (bh, bw), counted = NO_WORKSPACE[i]
+    cin, cout, n = 512, 96, 20
+    scheme = B.Scheme(cout, cin, bh, bw, reg, 2, 1)
+    if counted:
+        scheme.set_counts([[8 + (i + j) % 9 for j in range(cin // bw)] for i in range(cout // bh)])
+    w = torch.randn(cout, cin, device="cuda").to(torch.bfloat16)
+    layer = PackedLayer(scheme, B.BF16, w)
+    x = torch.randn(cin, n, device="cuda").to(torch.bfloat16)
+    y = torch.empty(cout, n, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        layer.linear(x, y, n, B.F32)
+    wm, xd = w.double() * layer.mask.view(cout, cin), x.double()
+    ref, bound = wm @ xd, 2 * (cin + 2) * 2.0 ** -24 * (wm.abs() @ xd.abs())   # fp32 sums in any order
+    for _ in range(3):
+        y.fill_(7.0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.all((y - ref).abs() <= bound)
+
+
+@pytest.mark.parametrize("i", range(len(NO_WORKSPACE)))
+def test_lists_outside_the_gathered_kernel_need_no_workspace(B, i):
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", f"from tests.test_pointwise_gpu import _captured; _captured({i})"],
+                       cwd=root, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr[-2000:]
