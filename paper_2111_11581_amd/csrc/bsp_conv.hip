@@ -353,6 +353,9 @@ static hipError_t launch_splitk_sum(const Plan &p, const void *part, int ks, int
 //  - large planes with many channels (more than 1024 64-pixel tiles) are memory-bound, and
 //    the deeper copy pipelines of the other kernels win: 256 -> 64 at 56x56 34 us, k_p1 41;
 //    64 -> 256 at 56x56 46, 49;
+//  - large outputs: of 38 layers and batches with 8 MB of fp32 or more, k_p1 took 1.15 times the
+//    others' time (0.95 to 1.4; it stores 16 bytes of every other group at a time), of 9 in front
+//    of k_pw with 32 MB of bf16 1.03 times (1.14 at worst; below that 0.7 to 0.95);
 //  - both would split the K loop: k_p1 wins with at most half as many parts (2048 -> 1000 at
 //    64 vectors 10.1 -> 9.2, 1024 -> 256 at 14x14, 8 images 17.5 -> 13.9), else it loses (4096
 //    -> 4096 at 128 vectors 22.8, 27.7; 2048 -> 512 at 7x7, 20 images 19.6, 25.5);
@@ -361,16 +364,16 @@ static hipError_t launch_splitk_sum(const Plan &p, const void *part, int ks, int
 //    512 -> 2048 at 7x7 27 -> 22; 1000 -> 700 at 100 vectors 15.8 -> 12.0);
 //  - only the other kernel would: k_p1's smaller tiles fill the chip without (5 images: 512
 //    -> 256 at 28x28 20.6 -> 8.4, 256 -> 1024 at 14x14 20.5 -> 6.5).
-// Choosing takes 3 us: a thread keeps its last choices (5 KB), by plan and by the number of
+// Choosing takes 3 us: a thread keeps its last choices (5 KB), by plan, output type and number of
 // pixel groups, through which alone the batch and the plane (no part of the plan's
 // fingerprint) enter.
-static bool p1_pick(const Plan &p, int n, P1Tiling *t) {
-    struct Choice { uint64_t plan; int64_t groups; int set, takes; P1Tiling t; };
+static bool p1_pick(const Plan &p, int n, int out_bf16, P1Tiling *t) {
+    struct Choice { uint64_t plan; int64_t groups; int set, out_bf16, takes; P1Tiling t; };
     static thread_local Choice kept[64];
     const int64_t groups = p1_groups(p, n);
     Choice &k = kept[(p.fingerprint ^ (p.fingerprint >> 29) ^ (uint64_t)(groups ^ (groups >> 7))) & 63];
-    if (!k.set || k.plan != p.fingerprint || k.groups != groups) {
-        Choice c{p.fingerprint, groups, 1, 0, {}};
+    if (!k.set || k.plan != p.fingerprint || k.groups != groups || k.out_bf16 != out_bf16) {
+        Choice c{p.fingerprint, groups, 1, out_bf16, 0, {}};
         // split where the other kernel would be, so that no call needs the workspace that
         // did without it
         const PwSplit sp = p.p1 ? PwSplit{1, p.S, 0} : pw_split(p, n);
@@ -378,9 +381,11 @@ static bool p1_pick(const Plan &p, int n, P1Tiling *t) {
         if (p1_choose(p, n, ks_max, 0, 0.0, p.n_mt_pad, &c.t)) {
             const int64_t tiles = div_up64(groups, kGroups);
             const int ks = p1_parts(p, c.t, groups, ks_max);
+            const int64_t y_bytes = groups * 4 * p.RK * (out_bf16 ? 2 : 4);
             if (p.p1) c.takes = 1;
             else if (tiles > 1024 && p.RK + p.Cin >= 256) c.takes = 0;
-            else if (!p.pl) c.takes = 1;
+            else if (!out_bf16 && y_bytes >= 8 << 20) c.takes = 0;
+            else if (!p.pl) c.takes = y_bytes < 32 << 20;
             else if (ks > 1) c.takes = 2 * ks <= sp.ks;
             else c.takes = sp.ks > 1 || p.S < 32 || tiles * div_up(p.n_groups * p.mt_per_group, 16) < 64;
         }
@@ -570,7 +575,7 @@ hipError_t launch_conv(const Plan &p, int n, const void *x, const uint8_t *tiles
                        int relu, int out_bf16, void *y, hipStream_t st, void *part) {
     if (p.pw && p.esize == 2 && !p.im2col && (p.p1 || (p.shared && p.SW == 1))) {
         P1Tiling t{p.NT, p.TM, p.TPG, p.lg_wp, p.SMAX, p.CC, p.cv_nch, p.CH_STRIDE, p.lds_buf};
-        if (!p.shared || p1_pick(p, n, &t)) return launch_p1(p, t, n, x, tiles, bias, relu, out_bf16, y, st);
+        if (!p.shared || p1_pick(p, n, out_bf16, &t)) return launch_p1(p, t, n, x, tiles, bias, relu, out_bf16, y, st);
     }
     if (p.pw) return launch_pw(p, n, x, tiles, bias, relu, out_bf16, y, st, part);
     if (stem_ok(p, x)) return launch_stem(p, n, x, tiles, bias, relu, out_bf16, y, st);
