@@ -187,9 +187,15 @@ struct Plan {
 bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv_or_null, bsp_dtype wdt,
                      int batch_for_linear, Plan *p);
 
-// Modelled time of a tiling of k_cv for a plan (see bsp_plan.cpp).
-double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG, int lg_wp);
-
+// Tiling of k_cv for n images of a plan, and (when asked for) its modelled time in us.  With
+// fewer images than the tiling was planned for, or where its units do not fit the registers,
+// smaller tiles (one m-tile per wave) run on the same packed layout, whose strides hold the
+// planned tile's rows, and spread a small layer over more CUs.  256 -> 256 at 28x28 -> 14x14, 5
+// images: 20.4 us with the planned tiles, 15.6 us with these.
+struct CvTiling {
+    int NT, TM, TPG, lg_wp;
+};
+CvTiling cv_tiling(const Plan &p, int n, double *us);
 
 // Tiling of k_p1: NT pixel tiles and TM m-tiles (TPG per list) per wave, 2^lg_wp waves along
 // pixels, chunks of SPC steps and CC channels (estimated nch of them), the channels' LDS

@@ -526,23 +526,8 @@ static hipError_t launch_cv(const Plan &p, int n, const void *x, const uint8_t *
     a.CH_STRIDE = p.CH_STRIDE; a.VS = p.VS;
     a.n_groups = p.n_groups; a.group_rows = p.group_rows; a.mt_per_group = p.mt_per_group;
     const int64_t groups = (int64_t)n * p.Ho * p.GPR;
-    // Fewer images than the tiling was planned for: smaller tiles (one m-tile per wave) run
-    // on the same packed layout, whose strides hold the planned tile's rows, and spread a
-    // small layer over more CUs.  256 -> 256 at 28x28 -> 14x14, 5 images: 20.4 us with the
-    // planned tiles, 15.6 us with these.
-    int NT = p.NT, TM = p.TM, TPG = p.TPG, lg_wp = p.lg_wp;
-    if (n < kNominalImages) {
-        const int n_mt = p.n_groups * p.mt_per_group;
-        double best = cv_cost(p, groups, n_mt, NT, TM, TPG, lg_wp);
-        for (int nt = 2; nt <= 4; nt *= 2) {
-            if (4 * nt > (4 * p.NT) << p.lg_wp || p.SMAX > cv_smax(1, nt)) continue;
-            const double c = cv_cost(p, groups, n_mt, nt, 1, 1, 0);
-            if (c < best) {
-                best = c;
-                NT = nt; TM = TPG = 1; lg_wp = 0;
-            }
-        }
-    }
+    const CvTiling t = cv_tiling(p, n, nullptr);
+    const int NT = t.NT, TM = t.TM, lg_wp = t.lg_wp;
     a.S = p.S; a.lg_wp = lg_wp;
     a.MBT = TM * (kCvWaves >> lg_wp);
     a.n_mb = div_up(p.n_groups * p.mt_per_group, a.MBT);
@@ -557,7 +542,7 @@ static hipError_t launch_cv(const Plan &p, int n, const void *x, const uint8_t *
     a.div_GPR = make_fastdiv((uint32_t)p.GPR);
     a.div_Ho = make_fastdiv((uint32_t)p.Ho);
     a.div_nmb = make_fastdiv((uint32_t)a.n_mb);
-    const cv::cv_fn fn = p.SW == 1 ? cv::pick_1(NT, TM, TPG, p.rowmap != 0) : cv::pick_2(NT, TM, TPG, p.rowmap != 0);
+    const cv::cv_fn fn = p.SW == 1 ? cv::pick_1(NT, TM, t.TPG, p.rowmap != 0) : cv::pick_2(NT, TM, t.TPG, p.rowmap != 0);
     if (!fn) return hipErrorInvalidValue;
     if (p.lds_total > 48 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -739,7 +739,7 @@ static double search_tiling(Plan *p, int span_req, double step_ch, int n_mt, int
 // Fitted to 640 measurements on gfx950 (27 layers, 3x3 at stride 1 and 2, planes 2x2 to
 // 56x56, column, row, punched and dense, every tiling): rms error 18%, and the tiling it
 // picks takes 1.04 of the best one's time on average (1.23 at worst).
-double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG, int lg_wp) {
+static double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG, int lg_wp) {
     const int TG = (4 * NT) << lg_wp, step = std::min(p.SH, p.KH);
     const double rows = 1.0 + (double)(TG - 1) / p.GPR;
     const double slots = rows * step + (p.KH - step) * (1.0 + (double)(TG - 1) / ((double)p.Ho * p.GPR));
@@ -752,6 +752,37 @@ double cv_cost(const Plan &p, int64_t groups, int n_mt, int NT, int TM, int TPG,
     const double serial = 6600.0 + p.cv_nch * 2870.0 + 100.0 * p.S * NT * (TM / TPG);
     const double a = (double)div_up64(n_wg, 256) * work, b = (double)div_up64(n_wg, 256 * occ) * serial;
     return a * a * a + b * b * b;
+}
+
+CvTiling cv_tiling(const Plan &p, int n, double *us) {
+    CvTiling t{p.NT, p.TM, p.TPG, p.lg_wp};
+    const int64_t groups = (int64_t)n * p.Ho * p.GPR;
+    const int n_mt = p.n_groups * p.mt_per_group;
+    // Units past the registers are loaded and stored round after round, which the fitted model
+    // does not hold: about 1000 cycles each (255 -> 18 at 64x64, 16-row punched 4x, 64 images: 132
+    // us in tiles of 10 rounds).
+    auto cost = [&](int NT, int TM, int TPG, int lg_wp) {
+        const int TG = (4 * NT) << lg_wp, step = std::min(p.SH, p.KH);
+        const double slots = (1.0 + (double)(TG - 1) / p.GPR) * step + (p.KH - step);
+        const double past = std::ceil(p.CC * slots * p.GPR / kCvRound) - cv_upt(p.SW);
+        const double c = std::cbrt(cv_cost(p, groups, n_mt, NT, TM, TPG, lg_wp));
+        const int occ = std::min(cv_wps(TM, NT) / 2, std::max(1, 160 * 1024 / (p.lds_total + 2048)));
+        const double wgs = (double)div_up64(groups, TG) * div_up(n_mt, TM * (kCvWaves >> lg_wp));
+        return past > 0 ? c + 1000.0 * past * p.cv_nch * std::ceil(wgs / (256.0 * occ)) : c;
+    };
+    const bool over = (int64_t)p.CC * p.NSLOT * p.GPR > (int64_t)cv_upt(p.SW) * kCvRound;
+    double best = cost(p.NT, p.TM, p.TPG, p.lg_wp);
+    for (int lg = 0; lg <= (over ? p.lg_wp : 0); ++lg)
+        for (int nt = 2; nt <= 4 && (n < kNominalImages || over); nt *= 2) {
+            if ((4 * nt) << lg > (4 * p.NT) << p.lg_wp || p.SMAX > cv_smax(1, nt)) continue;
+            const double c = cost(nt, 1, 1, lg);
+            if (c < best) {
+                best = c;
+                t = CvTiling{nt, 1, 1, lg};
+            }
+        }
+    if (us) *us = 1.15 * best / 2400.0;
+    return t;
 }
 
 // v or more, r mod 32.
@@ -1193,11 +1224,13 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     if (!p->is_linear && !im2col_inner && p->esize == 2 && p->KW == 3 && p->SW <= 2 && p->PW >= 1) {
         Plan c = *p, t = *p;
         const bool bounded = spans_bounded(*p);
-        auto time = [&](const Plan &q) {   // cubed
-            return cv_cost(q, (int64_t)kNominalImages * q.Ho * q.GPR, n_mt, q.NT, q.TM, q.TPG, q.lg_wp);
+        auto time = [&](const Plan &q) {
+            double us;
+            cv_tiling(q, kNominalImages, &us);
+            return us;
         };
         if (plan_cv(&c, window_req, step_ch, n_mt, mpg, !bounded) &&
-            (bounded || (plan_cv(&t, span_req, step_ch, n_mt, mpg, false) && time(c) <= 8 * time(t)))) {
+            (bounded || (plan_cv(&t, span_req, step_ch, n_mt, mpg, false) && time(c) <= 2 * time(t)))) {
             *p = c;
             finish_layout(p, n_mt, astep);
             return BSP_OK;

@@ -24,7 +24,7 @@ void check(int cin, int h, int w, int kh, int sh, int sw, int ph, int pw, const 
         memset(&a, 0, sizeof(a));
         cv_geometry(p, n, &a);
         const int groups = n * p.Ho * p.GPR;
-        for (int TG : {8, 16, (4 * p.NT) << p.lg_wp})   // the tiles the launcher may choose
+        for (int TG : {8, 16, 32, 64, 128, (4 * p.NT) << p.lg_wp})   // the tiles the launcher may choose
             for (int G0 = 0; G0 < groups; G0 += TG) {
                 const int g0 = G0 / p.GPR, g1 = (std::min(G0 + TG, groups) - 1) / p.GPR;
                 const int img0 = g0 / p.Ho, img1 = g1 / p.Ho;

@@ -53,6 +53,10 @@ CASES = [
     (3, 192, 10, 16, 32, 3, (2, 2), (1, 3), (16, 16), COL, 2, True, "bf16"),
     (1, 256, 12, 12, 33, 3, (1, 1), (2, 2), (16, 32), PUNCHED, 2, True, "bf16"),
     (1, 300, 3, 2, 33, 1, (1, 1), (0, 5), (0, 0), DENSE, 1, False, "bf16"),      # units with no column in the image
+    # units past the registers: smaller tiles of several pixel waves on the planned layout
+    (8, 32, 46, 46, 18, 3, (1, 1), (1, 1), (16, 64), COL, 4, True, "bf16"),
+    (8, 32, 46, 46, 31, 3, (1, 1), (1, 1), (16, 32), PUNCHED, 4, False, "f32"),
+    (66, 32, 46, 46, 18, 3, (2, 2), (1, 1), (16, 64), PUNCHED, 4, True, "bf16"),
 ]
 
 
