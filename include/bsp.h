@@ -213,11 +213,11 @@ bsp_status bsp_to_bcs(const bsp_scheme *scheme, const int32_t *indices, const in
  *  - layers with a kernel larger than 1x1 whose output plane has at most 16
  *    pixels, and bf16 layers with per-block-row lists (COL, PUNCHED, ROWCOL
  *    without counts) whose plane has at most 64 pixels (strided, or whose
- *    expanded input for 64 images stays within 24 MiB), except in both cases
- *    bf16 layers with 3-wide kernels at stride_w 1 or 2 and pad_w of at least 1
- *    whose plane has more than 4 pixels (they read x as it is), expand x into
- *    it (n x cin*kh*kw planes of Ho*Wo elements, rounded up to 8 for the bf16
- *    pipelined kernel);
+ *    expanded input for 64 images stays within 24 MiB), expand x into it (n x
+ *    cin*kh*kw planes of Ho*Wo elements, rounded up to 8 for the bf16
+ *    pipelined kernel); not those of them that are bf16 with 3-wide kernels at
+ *    stride_w 1 or 2, pad_w of at least 1 and a plane of more than 4 pixels,
+ *    unless they are COL or ROWCOL with whole-width blocks;
  *  - bf16 stride-1 pointwise layers (1x1, linear and the
  *    expanded layers above) whose output splits into at most 128 workgroup
  *    tiles (64 or 128 output pixels x 64 to 256 rows) split their K loop
@@ -225,7 +225,13 @@ bsp_status bsp_to_bcs(const bsp_scheme *scheme, const int32_t *indices, const in
  *    Ho*Wo floats).
  * Calls that use the workspace must not overlap on one device (other
  * streams, other threads), and the first one cannot be captured into a
- * graph. */
+ * graph.
+ * Layers that two kernels may run, by the batch (the 3-wide ones excepted
+ * above; lists of which both pointwise kernels make a plan): the second kernel
+ * does not use the workspace but buffers of the stream's own (up to 128 MiB
+ * for each of 8 streams of a device, kept until the process ends), and gives
+ * way to the first where there is none, as in a stream's first call inside a
+ * capture. */
 bsp_status bsp_conv2d(const bsp_scheme *scheme, const bsp_conv_shape *shape, bsp_dtype in_dt,
                       bsp_dtype out_dt, const void *x, const void *dev_tiles,
                       const float *bias_or_null, int32_t relu, void *y, void *stream);

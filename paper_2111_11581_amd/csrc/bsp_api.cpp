@@ -125,8 +125,8 @@ bsp_status bsp_conv2d(const bsp_scheme *scheme, const bsp_conv_shape *shape, bsp
     if (!scheme || !shape || !x || !dev_tiles || !y) return BSP_EINVAL;
     if (out_dt != BSP_F32 && out_dt != BSP_BF16) return BSP_EINVAL;
     if (shape->n < 0) return BSP_EINVAL;
-    Plan p;
-    bsp_status st = make_plan(scheme, shape, in_dt, 0, &p);
+    Plan p, alt;
+    bsp_status st = make_plan(scheme, shape, in_dt, 0, &p, &alt);
     if (st != BSP_OK) return st;
     if ((int64_t)shape->n * shape->cin * shape->h * shape->w > INT32_MAX ||
         (int64_t)shape->n * p.R * p.Ho * p.Wo > INT32_MAX || (int64_t)shape->n * p.Ho > INT32_MAX / 2)
@@ -140,6 +140,11 @@ bsp_status bsp_conv2d(const bsp_scheme *scheme, const bsp_conv_shape *shape, bsp
                    ? BSP_OK
                    : BSP_EDEVICE;
     }
+    hipError_t e;
+    if (p.alt && alt_takes(p, alt, shape->n, out_dt == BSP_BF16) &&
+        launch_alt(alt, shape, shape->n, x, (const uint8_t *)dev_tiles, bias, relu ? 1 : 0, out_dt == BSP_BF16, y,
+                   S(stream), &e))
+        return e == hipSuccess ? BSP_OK : BSP_EDEVICE;
     return launch_conv(p, shape->n, x, (const uint8_t *)dev_tiles, bias, relu ? 1 : 0,
                        out_dt == BSP_BF16, y, S(stream)) == hipSuccess
                ? BSP_OK
@@ -151,12 +156,17 @@ bsp_status bsp_linear(const bsp_scheme *scheme, int32_t batch, bsp_dtype in_dt, 
                       void *y, void *stream) {
     if (!scheme || !x || !dev_tiles || !y || batch < 0) return BSP_EINVAL;
     if (out_dt != BSP_F32 && out_dt != BSP_BF16) return BSP_EINVAL;
-    Plan p;
-    bsp_status st = make_plan(scheme, nullptr, in_dt, batch > 0 ? batch : 64, &p);
+    Plan p, alt;
+    bsp_status st = make_plan(scheme, nullptr, in_dt, batch > 0 ? batch : 64, &p, &alt);
     if (st != BSP_OK) return st;
     if ((int64_t)scheme->cols * batch > INT32_MAX || (int64_t)scheme->rows * batch > INT32_MAX)
         return BSP_EUNSUPPORTED;
     if (batch == 0) return BSP_OK;
+    hipError_t e;
+    if (p.alt && alt_takes(p, alt, batch, out_dt == BSP_BF16) &&
+        launch_alt(alt, nullptr, batch, x, (const uint8_t *)dev_tiles, bias, relu ? 1 : 0, out_dt == BSP_BF16, y,
+                   S(stream), &e))
+        return e == hipSuccess ? BSP_OK : BSP_EDEVICE;
     return launch_conv(p, batch, x, (const uint8_t *)dev_tiles, bias, relu ? 1 : 0, out_dt == BSP_BF16,
                        y, S(stream)) == hipSuccess
                ? BSP_OK

@@ -172,7 +172,10 @@ struct Plan {
     int NT, lg_wp;                // pixel tiles (16) per wave, log2 of the waves along pixels
     int cv_nch;                   // estimated chunks of the K loop
     int p1;                       // 1: the kernel of bf16 pointwise layers (k_p1) runs it (SMAX: steps of a chunk)
-    int p1_split;                 // 1: lists that k_p1 may split the K loop of
+    int p1_split;                 // 1: lists that k_pl takes too; k_p1 may split their K loop
+    int alt;                      // 1: tiles are packed for another plan too, whose kernel runs some batches
+    int alt_mt_pad, alt_g_pad;    // its padded m-tiles and list groups
+    int64_t off_alt;              // its list entries (uint16 channel numbers)
     // dev_tiles layout (bytes); with a row map, off_rowmap holds int32 rowmap[n_mt_pad * 16]
     // (kept output row of each computed row, 0 past RK) followed by the R - RK pruned rows
     int64_t off_chunks, off_desc, off_desc16, off_a, off_rowmap, off_pruned, off_counts, tile_bytes;
@@ -184,8 +187,11 @@ struct Plan {
 // Computes the plan; the geometry part ignores conv->n.  With conv_or_null == NULL
 // and batch_for_linear < 0 only the scheme and list structure are resolved.
 // Returns BSP_OK or an error.
+// With p->alt, *alt (when given) is the other plan of the same tiles.
 bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv_or_null, bsp_dtype wdt,
-                     int batch_for_linear, Plan *p);
+                     int batch_for_linear, Plan *p, Plan *alt = nullptr);
+// Whether the other plan is the faster one for n images (vectors).
+bool alt_takes(const Plan &p, const Plan &alt, int n, int out_bf16);
 
 // Tiling of k_cv for n images of a plan, and (when asked for) its modelled time in us.  With
 // fewer images than the tiling was planned for, or where its units do not fit the registers,
@@ -206,6 +212,9 @@ struct P1Tiling {
 double p1_cost(const Plan &p, const P1Tiling &t, int64_t groups, int ks);
 bool p1_choose(const Plan &p, int n, int ks_max, int span_req, double step_ch, int n_mt_pad, P1Tiling *best_t);
 int p1_parts(const Plan &p, const P1Tiling &t, int64_t groups, int ks_max);
+// Tiling of k_p1, and the most parts of a split K loop, for n images (vectors) of packed lists.
+P1Tiling p1_lists_tiling(const Plan &p, int n);
+int p1_lists_parts_max(const Plan &p, int n);
 // 4-pixel groups of a pointwise layer for n images (vectors), as k_p1 numbers them.
 int64_t p1_groups(const Plan &p, int n);
 

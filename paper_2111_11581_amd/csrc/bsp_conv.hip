@@ -426,24 +426,7 @@ static hipError_t launch_p1(const Plan &p, P1Tiling t, int n, const void *x, con
     a.x_total = p.is_linear ? (int64_t)p.Cin * n : images * p.Cin * (int64_t)a.x_cs;
     const int64_t groups = p1_groups(p, n);
     const int n_mt = p.n_groups * p.mt_per_group;
-    // Lists: offsets and chunks are packed for the planned tiles; smaller ones (one m-tile per
-    // wave) run on the same strides and spread a small batch over more CUs.  They are split
-    // only where any tiling of k_pl would be, so that no other call needs the workspace.
-    const bool small = p.p1_split && p.S >= 4 && div_up64(groups, kGroups) * div_up(n_mt, kWaves) <= 128;
-    const int ks_max = p.shared ? (!p.p1 && pw_split(p, n).ks > 1 ? 16 : 1) : small ? 16 : 1;
-    if (!p.shared && n < (p.is_linear ? kNominalVectors : kNominalImages)) {
-        P1Tiling u = t;
-        u.TM = u.TPG = 1;
-        u.lg_wp = 0;
-        double best = p1_cost(p, t, groups, p1_parts(p, t, groups, ks_max));
-        for (u.NT = 2; u.NT <= 4 && 4 * u.NT <= (4 * p.NT) << p.lg_wp; u.NT *= 2) {
-            const double c = p1_cost(p, u, groups, p1_parts(p, u, groups, ks_max));
-            if (c < best && u.SPC <= p1_smax(1, u.NT)) {
-                best = c;
-                t = u;
-            }
-        }
-    }
+    const int ks_max = !p.shared ? p1_lists_parts_max(p, n) : !p.p1 && pw_split(p, n).ks > 1 ? 16 : 1;
     a.lg_wp = t.lg_wp;
     a.MBT = t.TM * (kCvWaves >> t.lg_wp);
     a.n_mb = div_up(n_mt, a.MBT);
@@ -559,7 +542,8 @@ static hipError_t launch_cv(const Plan &p, int n, const void *x, const uint8_t *
 hipError_t launch_conv(const Plan &p, int n, const void *x, const uint8_t *tiles, const float *bias,
                        int relu, int out_bf16, void *y, hipStream_t st, void *part) {
     if (p.pw && p.esize == 2 && !p.im2col && (p.p1 || (p.shared && p.SW == 1))) {
-        P1Tiling t{p.NT, p.TM, p.TPG, p.lg_wp, p.SMAX, p.CC, p.cv_nch, p.CH_STRIDE, p.lds_buf};
+        P1Tiling t;
+        if (!p.shared) t = p1_lists_tiling(p, n);
         if (!p.shared || p1_pick(p, n, out_bf16, &t)) return launch_p1(p, t, n, x, tiles, bias, relu, out_bf16, y, st);
     }
     if (p.pw) return launch_pw(p, n, x, tiles, bias, relu, out_bf16, y, st, part);
@@ -728,18 +712,23 @@ static hipError_t workspace(size_t bytes, void **out) {
     return hipSuccess;
 }
 
+// Bytes of the expanded input for n images.
+static size_t im2col_bytes(const Plan &p, int n) {
+    const int64_t total = (int64_t)n * p.Cin * (p.xplane ? p.xplane : (int64_t)p.H * p.W);
+    return ((size_t)total * p.esize + 255) / 256 * 256;
+}
+
 hipError_t launch_conv_im2col(const Plan &p, const bsp_conv_shape &c, const void *x, const uint8_t *tiles,
-                              const float *bias, int relu, int out_bf16, void *y, hipStream_t st) {
+                              const float *bias, int relu, int out_bf16, void *y, hipStream_t st, void *ws) {
     // the 1x1 plan: Cin = cin kh kw, H x W = Ho x Wo, planes of xplane elements when padded
     const int64_t plane = p.xplane ? p.xplane : (int64_t)p.H * p.W;
     const int64_t total = (int64_t)c.n * p.Cin * plane;
     if (total <= 0) return hipSuccess;
     if (total > INT32_MAX) return hipErrorInvalidValue;
     // one workspace: the expanded input, then the partial sums of a split K loop
-    const size_t in_bytes = ((size_t)total * p.esize + 255) / 256 * 256;
+    const size_t in_bytes = im2col_bytes(p, c.n);
     const size_t part_bytes = pw_part_bytes(p, c.n);
-    void *ws = nullptr;
-    hipError_t e = workspace(in_bytes + part_bytes, &ws);
+    hipError_t e = ws ? hipSuccess : workspace(in_bytes + part_bytes, &ws);
     if (e != hipSuccess) return e;
     void *part = part_bytes ? (void *)((unsigned char *)ws + in_bytes) : nullptr;
     if (p.xplane) {
@@ -772,6 +761,70 @@ hipError_t launch_conv_im2col(const Plan &p, const bsp_conv_shape &c, const void
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_conv(p, c.n, ws, tiles, bias, relu, out_bf16, y, st, part);
+}
+
+// Buffers of launch_alt: one per stream, so that calls on different streams need no rule.  They
+// grow to at least twice their size and stay allocated (graphs may hold them): at most 2 x 64
+// MiB for each of 8 streams of a device.  Other streams, and larger needs, are refused.
+namespace {
+constexpr size_t kAltMaxBytes = 64u << 20;
+constexpr int kAltStreams = 8;
+struct AltBuffer {
+    hipStream_t st;
+    void *buf;
+    size_t size;
+    bool used;
+};
+std::mutex alt_mu;
+}  // namespace
+
+// The stream's buffer of at least `bytes`, or null.  alt_mu is held.
+static void *alt_buffer(size_t bytes, hipStream_t st) {
+    static AltBuffer all[64][kAltStreams];
+    int dev = 0;
+    if (bytes > kAltMaxBytes || st == hipStreamPerThread || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return nullptr;
+    AltBuffer *b = nullptr;
+    for (AltBuffer &e : all[dev])
+        if (e.used ? e.st == st : !b) {
+            b = &e;
+            if (e.used) break;
+        }
+    if (!b) return nullptr;
+    if (b->used && b->size >= bytes) return b->buf;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const size_t size = std::min(kAltMaxBytes, std::max(std::max(bytes, 2 * b->size), (size_t)1 << 20));
+    // another thread may be capturing: the allocation is no part of that
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    void *p = nullptr;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t e = hipMalloc(&p, size);
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    *b = AltBuffer{st, p, size, true};
+    return p;
+}
+
+bool launch_alt(const Plan &alt, const bsp_conv_shape *c, int n, const void *x, const uint8_t *tiles, const float *bias,
+                int relu, int out_bf16, void *y, hipStream_t st, hipError_t *e) {
+    const size_t bytes = (alt.im2col ? im2col_bytes(alt, n) : 0) + pw_part_bytes(alt, n);
+    std::unique_lock<std::mutex> lock(alt_mu, std::defer_lock);   // the launches that share the buffer stay together
+    void *ws = nullptr;
+    if (bytes) {
+        lock.lock();
+        ws = alt_buffer(bytes, st);
+        if (!ws) return false;
+    }
+    *e = alt.im2col ? launch_conv_im2col(alt, *c, x, tiles, bias, relu, out_bf16, y, st, ws)
+                    : launch_conv(alt, n, x, tiles, bias, relu, out_bf16, y, st, ws);
+    return true;
 }
 
 }  // namespace bsp

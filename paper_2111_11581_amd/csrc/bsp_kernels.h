@@ -45,12 +45,18 @@ hipError_t launch_stem(const Plan &p, int n, const void *x, const uint8_t *tiles
 // K loop is not split.
 size_t pw_part_bytes(const Plan &p, int n);
 
+// As launch_conv for the other plan of a layer's tiles (Plan::alt; c: the conv, or null for a
+// linear layer).  False, with nothing launched, when the buffer that it needs cannot be had (the
+// stream's first such call inside a capture, more than 64 MiB, out of memory).
+bool launch_alt(const Plan &alt, const bsp_conv_shape *c, int n, const void *x, const uint8_t *tiles, const float *bias,
+                int relu, int out_bf16, void *y, hipStream_t st, hipError_t *e);
+
 hipError_t launch_maxpool2x2(int dt, int n, int c, int h, int w, const void *x, void *y,
                              hipStream_t st);
 
 // A conv whose plan is a 1x1 layer over its im2col input (Plan::im2col): the input is
-// expanded into the library's per-device workspace, then the pointwise kernel runs.
+// expanded into ws, or (null) the library's per-device workspace, then the pointwise kernel runs.
 hipError_t launch_conv_im2col(const Plan &p, const bsp_conv_shape &c, const void *x, const uint8_t *tiles,
-                              const float *bias, int relu, int out_bf16, void *y, hipStream_t st);
+                              const float *bias, int relu, int out_bf16, void *y, hipStream_t st, void *ws = nullptr);
 
 }  // namespace bsp

@@ -310,8 +310,10 @@ __device__ __forceinline__ int2 slot_col(const CountTables &ct, const int32_t *_
 }
 
 __global__ void k_desc(DescArgs a, const int32_t *__restrict__ indices, const int32_t *__restrict__ rowptr,
-                       int32_t *__restrict__ desc) {
+                       int32_t *__restrict__ desc, uint16_t *__restrict__ cols, int cols_groups) {
     const int n = a.n_groups * a.LP;
+    // the other plan's list entries: the columns themselves (0 in its padding groups)
+    for (int e = n + blockIdx.x * blockDim.x + threadIdx.x; e < cols_groups * a.LP; e += gridDim.x * blockDim.x) cols[e] = 0;
     const int khw = a.KH * a.KW;
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
         const int g = e / a.LP, t = e - g * a.LP;
@@ -324,6 +326,7 @@ __global__ void k_desc(DescArgs a, const int32_t *__restrict__ indices, const in
             const int tt = t < gl.y ? t : gl.y - 1;
             q = gl.y == 0 ? 0 : (a.shared ? tt : indices[gl.x + tt]);
         }
+        if (cols) cols[e] = (uint16_t)q;
         const int c = q / khw, rs = q - c * khw;
         const int r = rs / a.KW, s = rs - r * a.KW;
         desc[e] = c * a.CH_STRIDE + (s % a.V) * a.VS + r * a.RS + (s / a.V) * a.V;
@@ -681,7 +684,8 @@ bsp_status pack_t(const Plan &p, const E *w, const uint8_t *mask, E *values, int
     int32_t *desc = (int32_t *)(tiles + p.off_desc);
     DescArgs da{p.shared, p.n_groups, p.L, p.LP, p.C, p.KH, p.KW, p.CH_STRIDE, p.RS, p.VS, std::max(p.V, 1),
                 ct, p.nbc, blk_cols};
-    k_desc<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(da, indices, rowptr, desc);
+    k_desc<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
+        da, indices, rowptr, desc, p.alt && !p.shared ? (uint16_t *)(tiles + p.off_alt) : nullptr, p.alt_g_pad);
     ATileArgs aa{p.shared, p.n_groups, p.mt_per_group, p.n_mt_pad, p.group_rows, p.S, p.L, p.RK, p.C, p.rowmap,
                  ct, p.nbc, blk_cols};
     const size_t na = (size_t)p.n_mt_pad * p.S * 512;

@@ -59,6 +59,7 @@ static int max_slots(int TG, int GPR, int Ho, int KH, int SH, int PH) {
 // check against the packed header.
 static void finish_layout(Plan *p, int n_mt, int astep) {
     p->n_mt_pad = p->cv || (p->pw && p->esize == 2) ? round_up(p->n_mb * p->MBT, kCvWaves) : p->n_mb * p->MBT;
+    p->n_mt_pad = std::max(p->n_mt_pad, p->alt_mt_pad);
     p->n_g_pad = p->shared ? 1 : std::max(p->n_groups, p->n_mb * p->MBG);
     if (p->shared) p->n_mt_pad = std::max(p->n_mt_pad, n_mt);
 
@@ -70,6 +71,10 @@ static void finish_layout(Plan *p, int n_mt, int astep) {
     p->off_pruned = p->off_rowmap + (int64_t)4 * (p->rowmap ? p->n_mt_pad * kMT : 0);
     p->off_counts = align256(p->off_pruned + (int64_t)4 * (p->rowmap ? p->R - p->RK : 0));
     p->tile_bytes = p->off_counts + (p->counts ? count_tables_bytes(p->nbr, p->nbc, p->L) : 0);
+    if (p->alt && !p->shared) {
+        p->off_alt = align256(p->tile_bytes);
+        p->tile_bytes = p->off_alt + (int64_t)2 * p->alt_g_pad * p->LP;
+    }
 
     const int fpv[] = {p->R, p->C, p->bh_eff, p->bw_eff, p->reg, p->rate, p->dt, p->n_groups,
                        p->mt_per_group, p->LP, p->S, p->CH_STRIDE, p->RS, p->LEFT, p->NSLOT,
@@ -77,6 +82,24 @@ static void finish_layout(Plan *p, int n_mt, int astep) {
                        p->MBT, p->MBG, p->n_mt_pad, p->n_g_pad, p->GE, p->NB, p->pw, p->NGR, p->VS, p->V,
                        p->rowmap, p->RK, p->khw, (int)p->counts_hash, p->counts != nullptr, p->pl, p->cv, p->p1, 14};
     p->fingerprint = fnv1a(fpv, (int)(sizeof(fpv) / sizeof(fpv[0])));
+    if (p->alt) {
+        const int av[] = {(int)p->fingerprint, (int)(p->fingerprint >> 32), p->alt_mt_pad, p->alt_g_pad};
+        p->fingerprint = fnv1a(av, 4);
+    }
+}
+
+// Makes *p, a finished plan, hold what plan q of the same lists needs too (the weight tiles
+// are the same; list entries as channel numbers are added), and points q at p's tiles.
+static void pack_for_both(Plan *p, Plan *q, int astep) {
+    p->alt = 1;
+    p->alt_mt_pad = q->n_mt_pad;
+    p->alt_g_pad = q->n_g_pad;
+    finish_layout(p, p->n_groups * p->mt_per_group, astep);
+    q->n_mt_pad = p->n_mt_pad;
+    q->off_chunks = p->off_chunks; q->off_desc = p->off_desc; q->off_desc16 = p->off_alt; q->off_a = p->off_a;
+    q->off_rowmap = p->off_rowmap; q->off_pruned = p->off_pruned; q->off_counts = p->off_counts;
+    q->tile_bytes = p->tile_bytes;
+    q->fingerprint = p->fingerprint;
 }
 
 // Tiling of a pointwise layer for the pointwise kernel.  The patch row of a channel
@@ -350,6 +373,32 @@ int p1_parts(const Plan &p, const P1Tiling &t, int64_t groups, int ks_max) {
                           div_up(p.n_groups * p.mt_per_group, t.TM * (kCvWaves >> t.lg_wp));
     if (ks_max < 2 || units > 128 || units < 1 || t.nch < 2) return 1;
     return (int)std::min<int64_t>(std::min<int64_t>(ks_max, 256 / units), t.nch);
+}
+
+// Lists: offsets and chunks are packed for the planned tiles; smaller ones (one m-tile per
+// wave) run on the same strides and spread a small batch over more CUs.  They are split only
+// where any tiling of k_pl would be, so that no other call needs the workspace.
+int p1_lists_parts_max(const Plan &p, int n) {
+    const int n_mt = p.n_groups * p.mt_per_group;
+    return p.p1_split && p.S >= 4 && div_up64(p1_groups(p, n), kGroups) * div_up(n_mt, kWaves) <= 128 ? 16 : 1;
+}
+P1Tiling p1_lists_tiling(const Plan &p, int n) {
+    P1Tiling t{p.NT, p.TM, p.TPG, p.lg_wp, p.SMAX, p.CC, p.cv_nch, p.CH_STRIDE, p.lds_buf};
+    if (n >= (p.is_linear ? kNominalVectors : kNominalImages)) return t;
+    const int64_t groups = p1_groups(p, n);
+    const int ks_max = p1_lists_parts_max(p, n);
+    P1Tiling u = t;
+    u.TM = u.TPG = 1;
+    u.lg_wp = 0;
+    double best = p1_cost(p, t, groups, p1_parts(p, t, groups, ks_max));
+    for (u.NT = 2; u.NT <= 4 && 4 * u.NT <= (4 * p.NT) << p.lg_wp; u.NT *= 2) {
+        const double c = p1_cost(p, u, groups, p1_parts(p, u, groups, ks_max));
+        if (c < best && u.SPC <= p1_smax(1, u.NT)) {
+            best = c;
+            t = u;
+        }
+    }
+    return t;
 }
 
 // Layout for k_p1 alone (stride 2; per-block-row lists), tiled for the nominal batch.
@@ -785,6 +834,12 @@ CvTiling cv_tiling(const Plan &p, int n, double *us) {
     return t;
 }
 
+static double cv_us(const Plan &p, int n) {
+    double us;
+    cv_tiling(p, n, &us);
+    return us;
+}
+
 // v or more, r mod 32.
 static int pad_to(int v, int r) { return v + ((r - v) % 32 + 32) % 32; }
 
@@ -899,8 +954,63 @@ constexpr int kIm2colMaxPixels = 16;
 constexpr int kIm2colListPixels = 64;
 constexpr int64_t kIm2colListBytes = 24ll << 20;
 
+// The plan of a conv as a 1x1 layer over its im2col input.
+static bsp_status plan_im2col(const bsp_scheme *s, const bsp_conv_shape *conv, int ho, int wo, bsp_dtype wdt,
+                              int batch_for_linear, Plan *p) {
+    if ((int64_t)conv->cin * conv->kh * conv->kw != s->cols) return BSP_EINVAL;
+    if (s->regularity == BSP_PUNCHED && conv->kh * conv->kw != s->khw) return BSP_EINVAL;
+    const bsp_conv_shape c2 = {conv->n, s->cols, ho, wo, 1, 1, 1, 1, 0, 0};
+    const bsp_status st = make_plan_impl(s, &c2, wdt, batch_for_linear, p, true);
+    // the pipelined kernel reads the im2col planes padded to whole granules
+    if (st == BSP_OK && p->pl) p->xplane = round_up(ho * wo, p->GE);
+    return st;
+}
+
+// Time (us) of the im2col route on k_pl for n images: the launches, the expanded input
+// written and read, the K loop of the workgroups a CU runs in turn and the partial sums.
+// Fitted to 344 layers and batches of 3-wide convs (planes of 16 to 64 pixels): rms error 12%.
+static double im2col_us(const Plan &p, int n) {
+    const int64_t units = div_up64((int64_t)n * p.xplane / 4, kGroups * p.NSUB) * p.n_mb;
+    int ks = 1;
+    if (units <= 128 && p.S >= 4) ks = std::min((int)std::min<int64_t>(16, 256 / units), p.S / 2);
+    const double mb = 2e-6 * n * p.Cin * p.xplane, part = ks > 1 ? 4e-6 * ks * n * p.R * p.H * p.W : 0.0;
+    return 8.3 + 0.76 * mb + 0.55 * (double)div_up64(units * ks, 256) * div_up(p.S, ks) + 0.42 * part + (ks > 1 ? 1.5 : 0.0);
+}
+
+// Times (us) for n images (vectors) of a layer with per-block-row lists on k_p1, which stages
+// every channel that a chunk's lists span, and on k_pl, which stages the listed ones for each
+// list group.  Fitted to 1078 layers and batches (1x1 at stride 1 and linear, column blocks 2x to
+// 4x): rms errors 11% and 10%.
+static double p1_list_us(const Plan &p, int n, int y_bytes) {
+    const P1Tiling t = p1_lists_tiling(p, n);
+    const int64_t groups = p1_groups(p, n);
+    const int ks = p1_parts(p, t, groups, p1_lists_parts_max(p, n));
+    const double px = (double)n * (p.is_linear ? 1 : p.H * p.W);
+    const double staged = 2e-6 * px * t.CC * t.nch * div_up(p.n_groups * p.mt_per_group, t.TM * (kCvWaves >> t.lg_wp));
+    return 3.4 + 0.48 * std::cbrt(p1_cost(p, t, groups, ks)) / 2400.0 + 0.15 * staged + 0.16e-6 * px * p.Cin +
+           0.27e-6 * px * p.R * y_bytes + (ks > 1 ? 2.6e-6 * ks * px * p.R + 0.7 : 0.0);
+}
+static double pl_list_us(const Plan &p, int n, int y_bytes) {
+    const int64_t n_pt = div_up64(p1_groups(p, n), kGroups * p.NSUB), units = n_pt * p.n_mb;
+    int ks = 1;
+    if (units <= 128 && p.S >= 4) ks = std::min((int)std::min<int64_t>(16, 256 / units), p.S / 2);
+    const int steps = div_up(p.S, ks);
+    const int64_t wpm = ks > 1 ? n_pt : std::min<int64_t>(n_pt, div_up(256, p.n_mb));
+    const double tiles = (double)div_up64(n_pt, wpm) * div_up64(wpm * p.n_mb * ks, 256);   // a CU's, in turn
+    const double px = (double)n * (p.is_linear ? 1 : p.H * p.W);
+    return 5.3 + tiles * (0.40 * div_up(steps, p.SMAX) + 0.145 * steps * p.MBG * p.NSUB) + 0.185e-6 * px * p.R * y_bytes +
+           0.48e-3 * p.n_groups * p.mt_per_group * p.S + (ks > 1 ? 2.4e-6 * ks * px * p.R + 2.0 : 0.0);
+}
+
+// 0.92: at equal modelled times the planned kernel was the faster one more often.
+bool alt_takes(const Plan &p, const Plan &alt, int n, int out_bf16) {
+    const int y_bytes = out_bf16 ? 2 : 4;
+    return p.cv ? im2col_us(alt, n) < 0.92 * cv_us(p, n)
+                : pl_list_us(alt, n, y_bytes) < 0.92 * p1_list_us(p, n, y_bytes);
+}
+
 static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt,
-                                int batch_for_linear, Plan *p) {
+                                int batch_for_linear, Plan *p, Plan *alt) {
     if (s && conv && conv->kh > 0 && conv->kw > 0 && (conv->kh > 1 || conv->kw > 1) && conv->stride_h > 0 &&
         conv->stride_w > 0 && conv->pad_h >= 0 && conv->pad_w >= 0 && conv->cin > 0 &&
         conv->h + 2 * conv->pad_h >= conv->kh && conv->w + 2 * conv->pad_w >= conv->kw) {
@@ -920,20 +1030,46 @@ static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv,
               (int64_t)kNominalImages * kcols * round_up((int)plane, 8) * 2 <= kIm2colListBytes));
         if (cv) {
             const bsp_status st = make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
-            // else as a layer that is not 3 wide; so too lists that k_cv would store with zeros
-            if (st == BSP_OK && p->cv && !(expand && lists && p->shared)) return st;
+            // else as a layer that is not 3 wide.  k_cv walks its chunks in series, the im2col route
+            // splits its K loop: dense 512 at 4x4, 4 images, 50 and 14 us; 16x32 column blocks 4x,
+            // 512 at 14x14 at stride 2, 64 images, 30 and 80 us.  Where either may win, tiles are
+            // packed for both and the batch decides.
+            if (st == BSP_OK && p->cv) {
+                Plan q;
+                if (!expand || plan_im2col(s, conv, ho, wo, wdt, batch_for_linear, &q) != BSP_OK || !q.pl) return st;
+                if (p->shared == q.shared) {
+                    bool any = false;
+                    for (int n = 1; n <= kNominalImages; n *= 4) any |= alt_takes(*p, q, n, 1);
+                    if (any) {
+                        pack_for_both(p, &q, 1024);
+                        *alt = q;
+                    }
+                    return st;
+                }
+                // lists that k_cv stores with zeros: one or the other
+                if (cv_us(*p, kNominalImages) * std::pow(cv_us(*p, 4), 1.5) <=
+                    im2col_us(q, kNominalImages) * std::pow(im2col_us(q, 4), 1.5))
+                    return st;
+            }
         }
-        if (expand) {
-            if ((int64_t)conv->cin * conv->kh * conv->kw != s->cols) return BSP_EINVAL;
-            if (s->regularity == BSP_PUNCHED && conv->kh * conv->kw != s->khw) return BSP_EINVAL;
-            const bsp_conv_shape c2 = {conv->n, conv->cin * conv->kh * conv->kw, ho, wo, 1, 1, 1, 1, 0, 0};
-            const bsp_status st = make_plan_impl(s, &c2, wdt, batch_for_linear, p, true);
-            // the pipelined kernel reads the im2col planes padded to whole granules
-            if (st == BSP_OK && p->pl) p->xplane = (int)round_up((int)plane, p->GE);
-            return st;
-        }
+        if (expand) return plan_im2col(s, conv, ho, wo, wdt, batch_for_linear, p);
     }
-    return make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
+    const bsp_status st = make_plan_impl(s, conv, wdt, batch_for_linear, p, false);
+    if (st != BSP_OK || !p->p1 || !p->p1_split) return st;
+    // lists that both k_p1 and k_pl take (454 -> 24 at 25x25, 64-row blocks 4x, 64 images, 24 and 11
+    // us; 768 -> 3072 at 256 vectors, 4x, 8.0 and 15.7)
+    Plan q = *p;
+    plan_pl(&q, q.n_groups * q.mt_per_group, 1024);
+    q.p1 = 0;
+    finish_layout(&q, q.n_groups * q.mt_per_group, 1024);
+    bool any = false;
+    for (int n = 1; n <= (p->is_linear ? 1024 : kNominalImages); n *= 4)
+        any |= alt_takes(*p, q, n, 0) || alt_takes(*p, q, n, 1);
+    if (any) {
+        pack_for_both(p, &q, 1024);
+        *alt = q;
+    }
+    return st;
 }
 
 // A plan is a pure function of the values below (the batch does not enter), so a thread
@@ -950,15 +1086,18 @@ struct PlanCache {
     struct Entry {
         PlanKey key;
         bool used;
-        Plan plan;
+        Plan plan, alt;
     };
     Entry e[kSets][kWays];
     int next[kSets];
 };
 }  // namespace
 
-bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt, int batch_for_linear, Plan *p) {
-    if (!s || !p || s->counts) return make_plan_new(s, conv, wdt, batch_for_linear, p);
+bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype wdt, int batch_for_linear, Plan *p,
+                     Plan *alt) {
+    Plan spare;
+    if (!alt) alt = &spare;
+    if (!s || !p || s->counts) return make_plan_new(s, conv, wdt, batch_for_linear, p, alt);
     PlanKey key;
     std::memset(&key, 0, sizeof(key));
     const int v[] = {s->rows, s->cols, s->bh, s->bw, s->regularity, s->rate, s->khw, (int)wdt,
@@ -971,20 +1110,22 @@ bsp_status make_plan(const bsp_scheme *s, const bsp_conv_shape *conv, bsp_dtype 
     }
     static thread_local std::unique_ptr<PlanCache> cache;
     if (!cache) cache.reset(new (std::nothrow) PlanCache());
-    if (!cache) return make_plan_new(s, conv, wdt, batch_for_linear, p);
+    if (!cache) return make_plan_new(s, conv, wdt, batch_for_linear, p, alt);
     const uint64_t h = fnv1a(key.v, (int)(sizeof(key.v) / sizeof(key.v[0])));
     const int set = (int)((h ^ (h >> 32)) % PlanCache::kSets);
     for (PlanCache::Entry &e : cache->e[set])
         if (e.used && std::memcmp(&e.key, &key, sizeof(key)) == 0) {
             *p = e.plan;
+            if (p->alt) *alt = e.alt;
             return BSP_OK;
         }
-    const bsp_status st = make_plan_new(s, conv, wdt, batch_for_linear, p);
+    const bsp_status st = make_plan_new(s, conv, wdt, batch_for_linear, p, alt);
     if (st == BSP_OK) {
         PlanCache::Entry &e = cache->e[set][cache->next[set]];
         cache->next[set] = (cache->next[set] + 1) % PlanCache::kWays;
         e.key = key;
         e.plan = *p;
+        if (p->alt) e.alt = *alt;
         e.used = true;
     }
     return st;
@@ -1224,13 +1365,9 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
     if (!p->is_linear && !im2col_inner && p->esize == 2 && p->KW == 3 && p->SW <= 2 && p->PW >= 1) {
         Plan c = *p, t = *p;
         const bool bounded = spans_bounded(*p);
-        auto time = [&](const Plan &q) {
-            double us;
-            cv_tiling(q, kNominalImages, &us);
-            return us;
-        };
         if (plan_cv(&c, window_req, step_ch, n_mt, mpg, !bounded) &&
-            (bounded || (plan_cv(&t, span_req, step_ch, n_mt, mpg, false) && time(c) <= 2 * time(t)))) {
+            (bounded || (plan_cv(&t, span_req, step_ch, n_mt, mpg, false) &&
+                         cv_us(c, kNominalImages) <= 2 * cv_us(t, kNominalImages)))) {
             *p = c;
             finish_layout(p, n_mt, astep);
             return BSP_OK;

@@ -31,3 +31,8 @@ def test_no_read_outside_the_input(tmp_path):
 def test_windows_hold_every_step(tmp_path):
     """No mask that a scheme allows is refused for its kept columns lying far apart."""
     _run("windows", tmp_path)
+
+
+def test_layers_packed_for_two_kernels(tmp_path):
+    """Their plans agree on the tiles and each kernel gets the batches it measured faster at."""
+    _run("both", tmp_path)
