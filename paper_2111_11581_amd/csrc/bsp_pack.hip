@@ -161,9 +161,9 @@ __global__ void k_check_count(const unsigned int *count, unsigned int k, int *fl
 
 // Kept-column list of block-row i, written at rowptr[i] (offsets computed on the host
 // from the scheme); the block-row's first row holds its kept columns.  A thread scans 8
-// consecutive columns per round, so 4608 columns take 3 rounds of barriers (one column per
-// thread: 18); the chain of rounds bounds it (512 x 4608 in 16-row blocks: 12.5 us with one
-// column per thread, 10.1 us).
+// consecutive columns per round (one 8-byte load of each row), so 4608 columns take 3 rounds of
+// barriers (one column per thread: 18); the chain of rounds bounds it (512 x 4608 in 16-row
+// blocks: 12.5 us with one column per thread, 10.1 us with 8 loads of a byte).
 __global__ void k_col_lists(const uint8_t *__restrict__ mask, int R, int C, int bh, int any_row,
                             const int32_t *__restrict__ rowptr, int32_t *__restrict__ indices, int *flag) {
     __shared__ int wave_tot[4];
@@ -175,12 +175,24 @@ __global__ void k_col_lists(const uint8_t *__restrict__ mask, int R, int C, int 
     for (int q0 = 0; q0 < C; q0 += 256 * 8) {
         const int q = q0 + threadIdx.x * 8;
         uint32_t keep = 0;
-        for (int j = 0; j < 8 && q + j < C; ++j)
-            for (int r = 0; r < rows; ++r)
-                if (mr[(size_t)r * C + q + j]) {
-                    keep |= 1u << j;
-                    break;
-                }
+        if (q + 8 <= C) {   // the mask's bytes are 0 or 1 (validated)
+            struct __attribute__((packed)) U2 { uint32_t lo, hi; };
+            U2 v = *(const U2 *)(mr + q);
+            for (int r = 1; r < rows; ++r) {
+                const U2 o = *(const U2 *)(mr + (size_t)r * C + q);
+                v.lo |= o.lo;
+                v.hi |= o.hi;
+            }
+            // bytes' lowest bits to bits 0 .. 3 (the products do not overlap)
+            keep = ((v.lo * 0x01020408u) >> 24 & 0xfu) | ((v.hi * 0x01020408u) >> 24 & 0xfu) << 4;
+        } else {
+            for (int j = 0; q + j < C; ++j)
+                for (int r = 0; r < rows; ++r)
+                    if (mr[(size_t)r * C + q + j]) {
+                        keep |= 1u << j;
+                        break;
+                    }
+        }
         const int n = __popc(keep);
         int pre = n;   // inclusive prefix over the wave
         for (int d = 1; d < 64; d *= 2) {
@@ -395,12 +407,11 @@ __global__ void k_rowmap(const int32_t *__restrict__ kept, int RK, int R, int32_
     }
 }
 
-// Channels that step s spans over all lists: one wave per step, a list per lane (32 lists
-// of 36 steps: a thread's serial walk over the lists 12.3 us, 2.6 us).
-__global__ void k_step_spans(const int32_t *__restrict__ desc, int n_groups, int LP, int CH_STRIDE, int4 *table) {
-    const int s = blockIdx.x;
+// Channels that step s spans over all lists (one wave, a list per lane: 32 lists of 36 steps
+// with a thread's serial walk over the lists 12.3 us, 2.6 us).
+__device__ __forceinline__ int2 step_span(const int32_t *__restrict__ desc, int n_groups, int LP, int CH_STRIDE, int s) {
     int lo = 0x7fffffff, hi = -1;
-    for (int g = threadIdx.x; g < n_groups; g += 64) {
+    for (int g = threadIdx.x & 63; g < n_groups; g += 64) {
         lo = min(lo, desc[(size_t)g * LP + 32 * s]);
         hi = max(hi, desc[(size_t)g * LP + 32 * s + 31]);
     }
@@ -408,20 +419,14 @@ __global__ void k_step_spans(const int32_t *__restrict__ desc, int n_groups, int
         lo = min(lo, __shfl_xor(lo, d));
         hi = max(hi, __shfl_xor(hi, d));
     }
-    if (threadIdx.x == 0) table[s] = make_int4(lo / CH_STRIDE, hi / CH_STRIDE, 0, 0);
+    return make_int2(lo / CH_STRIDE, hi / CH_STRIDE);
 }
 
-__global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int lo_max, int *n_chunks, int *flag) {
-    extern __shared__ int spans[];  // 2*S
-    for (int s = threadIdx.x; s < S; s += blockDim.x) {
-        spans[2 * s] = table[s].x;
-        spans[2 * s + 1] = table[s].y;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
+// Chunks of steps whose spans fit CC channels (one thread; spans: 2 S ints); n_chunks last.
+// k_cv and k_p1 stage CC channels of every chunk: none may start past Cin - CC (lo_max).
+__device__ __forceinline__ int build_chunks(const int *spans, int4 *table, int S, int CC, int smax, int lo_max, int *flag) {
     int nc = 0, s = 0;
     while (s < S) {
-        // k_cv and k_p1 stage CC channels of every chunk: none may start past Cin - CC (lo_max)
         const int lo = min(spans[2 * s], lo_max);
         int hi = spans[2 * s + 1];
         if (hi - lo + 1 > CC) {
@@ -438,44 +443,102 @@ __global__ void k_build_chunks(int4 *table, int S, int CC, int smax, int lo_max,
         table[nc++] = make_int4(s, e, lo, hi - lo + 1);
         s = e;
     }
-    *n_chunks = nc;
+    return nc;
 }
 
-// 16-bit chunk-relative gather offsets: each step belongs to one chunk (a range of
-// steps); the offset of a kept column relative to the chunk's first channel is
-// below CC * CH_STRIDE, which fits 16 bits by the LDS budget.
-__global__ void k_desc16(const int32_t *__restrict__ desc, const int4 *__restrict__ table,
-                         const int *n_chunks_p, int n_groups, int LP, int CH_STRIDE, int cv,
-                         uint16_t *__restrict__ desc16, int *flag) {
-    const int n = n_groups * LP;
-    const int nch = *n_chunks_p;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-        const int s = (e % LP) / 32;
-        int a = 0, b = nch;   // the last chunk that starts at or before step s
-        while (b - a > 1) {
-            const int m = (a + b) >> 1;
-            if (table[m].x <= s) a = m;
-            else b = m;
+// 16-bit chunk-relative gather offsets of step s, whose chunk starts at channel lo (-1: none),
+// for lists g0, g0 + dg, .. of n_g_pad (0, a valid patch position, past the n_groups there are),
+// by 32 threads: below CC * CH_STRIDE, which fits 16 bits by the LDS budget.  cv (k_cv, k_p1):
+// entries t = 8 kg + 4 h + q of a step at 2 (4 kg + q) + h (a lane's two reads).
+__device__ __forceinline__ void step_offsets(const int32_t *__restrict__ desc, int n_groups, int n_g_pad, int LP,
+                                             int CH_STRIDE, int cv, int s, int lo, int g0, int dg,
+                                             uint16_t *__restrict__ desc16, int *flag) {
+    const int t = threadIdx.x & 31, d = cv ? 2 * (4 * (t >> 3) + (t & 3)) + ((t >> 2) & 1) : t;
+    for (int g = g0; g < n_g_pad; g += dg) {
+        const size_t at = (size_t)g * LP + 32 * s;
+        int off = 0;
+        if (g < n_groups) {
+            off = lo < 0 ? -1 : desc[at + t] - lo * CH_STRIDE;
+            if (off < 0 || off > 0xffff) {
+                atomicOr(flag, 2);
+                off = 0;
+            }
         }
-        const int lo = nch > 0 && s >= table[a].x && s < table[a].y ? table[a].z : -1;
-        const int off = desc[e] - lo * CH_STRIDE;
-        // k_cv, k_p1: entries t = 8 kg + 4 h + q of a step at 2 (4 kg + q) + h (a lane's two reads)
-        const int t = e & 31;
-        const int d = cv ? (e & ~31) + 2 * (4 * (t >> 3) + (t & 3)) + ((t >> 2) & 1) : e;
-        if (lo < 0 || off < 0 || off > 0xffff) {
-            atomicOr(flag, 2);
-            desc16[d] = 0;
-        } else {
-            desc16[d] = (uint16_t)off;
+        desc16[at + d] = (uint16_t)off;
+    }
+}
+
+struct ChunkArgs {
+    const int32_t *desc;
+    int n_groups, n_g_pad, LP, S, CH_STRIDE, CC, smax, lo_max, cv;
+    int4 *table;
+    int *n_chunks;
+    uint16_t *desc16;
+    int *flag;
+};
+
+// Spans, chunks and offsets in one workgroup: for the lists of a small layer three launches
+// (and a fourth for the padding) cost more than the work.
+__global__ __launch_bounds__(1024) void k_chunks(ChunkArgs a) {
+    extern __shared__ int lds_chunks[];   // 2 S spans, then S first channels
+    int *spans = lds_chunks, *first = lds_chunks + 2 * a.S;
+    const int wave = threadIdx.x >> 6;
+    for (int s = wave; s < a.S; s += 16) {
+        const int2 v = step_span(a.desc, a.n_groups, a.LP, a.CH_STRIDE, s);
+        if ((threadIdx.x & 63) == 0) {
+            spans[2 * s] = v.x;
+            spans[2 * s + 1] = v.y;
+            first[s] = -1;
         }
     }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int nc = build_chunks(spans, a.table, a.S, a.CC, a.smax, a.lo_max, a.flag);
+        for (int c = 0; c < nc; ++c) {
+            const int4 t = a.table[c];
+            for (int s = t.x; s < t.y; ++s) first[s] = t.z;
+        }
+        *a.n_chunks = nc;
+    }
+    __syncthreads();
+    for (int s = wave; s < a.S; s += 16)
+        step_offsets(a.desc, a.n_groups, a.n_g_pad, a.LP, a.CH_STRIDE, a.cv, s, first[s], (threadIdx.x >> 5) & 1, 2,
+                     a.desc16, a.flag);
+}
+
+// The same for large layers: one wave per step; one thread; one workgroup per step.
+__global__ void k_step_spans(ChunkArgs a) {
+    const int2 v = step_span(a.desc, a.n_groups, a.LP, a.CH_STRIDE, blockIdx.x);
+    if (threadIdx.x == 0) a.table[blockIdx.x] = make_int4(v.x, v.y, 0, 0);
+}
+__global__ void k_build_chunks(ChunkArgs a) {
+    extern __shared__ int lds_chunks[];   // 2 S
+    for (int s = threadIdx.x; s < a.S; s += blockDim.x) {
+        lds_chunks[2 * s] = a.table[s].x;
+        lds_chunks[2 * s + 1] = a.table[s].y;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *a.n_chunks = build_chunks(lds_chunks, a.table, a.S, a.CC, a.smax, a.lo_max, a.flag);
+}
+__global__ void k_desc16(ChunkArgs a) {
+    const int s = blockIdx.x, nch = *a.n_chunks;
+    int b = 0, e = nch;   // the last chunk that starts at or before step s
+    while (e - b > 1) {
+        const int m = (b + e) >> 1;
+        if (a.table[m].x <= s) b = m;
+        else e = m;
+    }
+    const int lo = nch > 0 && s >= a.table[b].x && s < a.table[b].y ? a.table[b].z : -1;
+    step_offsets(a.desc, a.n_groups, a.n_g_pad, a.LP, a.CH_STRIDE, a.cv, s, lo, threadIdx.x >> 5, blockDim.x >> 5, a.desc16,
+                 a.flag);
 }
 
 // 16-bit channels of the pointwise kernel's gathered lists (the lists' channel
 // numbers themselves; no chunks).
-__global__ void k_desc16_abs(const int32_t *__restrict__ desc, int n, uint16_t *__restrict__ desc16, int *flag) {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-        const int v = desc[e];
+// Entries n .. n_pad - 1 (the padding groups of the last m-block) are 0.
+__global__ void k_desc16_abs(const int32_t *__restrict__ desc, int n, int n_pad, uint16_t *__restrict__ desc16, int *flag) {
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n_pad; e += gridDim.x * blockDim.x) {
+        const int v = e < n ? desc[e] : 0;
         if (v < 0 || v > 0xffff) {
             atomicOr(flag, 2);
             desc16[e] = 0;
@@ -568,6 +631,11 @@ __global__ void k_bcs(const int32_t *__restrict__ indices, const int32_t *__rest
         *n_runs = s_runs;
     }
 }
+
+// List entries up to which one workgroup builds the chunks (prune, pack and unpack of a layer
+// of 16-row column blocks: 18432 entries 112 us with three launches, 92 with one; 36864 entries
+// 119 and 107; 73728 entries 128 either way).
+constexpr int64_t kOneWorkgroupEntries = 65536;
 
 inline int grid_for(size_t n) { return (int)std::max<size_t>(1, std::min<size_t>(8192, (n + 255) / 256)); }
 
@@ -684,7 +752,9 @@ bsp_status pack_t(const Plan &p, const E *w, const uint8_t *mask, E *values, int
     int32_t *desc = (int32_t *)(tiles + p.off_desc);
     DescArgs da{p.shared, p.n_groups, p.L, p.LP, p.C, p.KH, p.KW, p.CH_STRIDE, p.RS, p.VS, std::max(p.V, 1),
                 ct, p.nbc, blk_cols};
-    k_desc<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
+    // k_p1 and k_pl walk the channels of an identity list themselves
+    const bool identity = p.shared && (p.p1 || p.pl);
+    if (!identity) k_desc<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
         da, indices, rowptr, desc, p.alt && !p.shared ? (uint16_t *)(tiles + p.off_alt) : nullptr, p.alt_g_pad);
     ATileArgs aa{p.shared, p.n_groups, p.mt_per_group, p.n_mt_pad, p.group_rows, p.S, p.L, p.RK, p.C, p.rowmap,
                  ct, p.nbc, blk_cols};
@@ -696,27 +766,22 @@ bsp_status pack_t(const Plan &p, const E *w, const uint8_t *mask, E *values, int
         k_fill<int32_t><<<grid_for(nrm), 256, 0, st>>>(rm, nrm, 0);
         k_rowmap<<<grid_for(p.R), 256, 0, st>>>(indices, p.RK, p.R, rm, (int32_t *)(tiles + p.off_pruned));
     }
-    if (p.p1 && p.shared) {
-        // identity lists: the kernel walks the channels itself
-    } else if (p.pl && !p.shared) {
+    if (p.pl && !p.shared) {
         // the pointwise kernel with gathered lists reads the channels of the lists (its
         // plan's channel stride is 1) and no chunk table
-        k_desc16_abs<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
-            desc, p.n_groups * p.LP, (uint16_t *)(tiles + p.off_desc16), flag);
-    } else {
-        int4 *table = (int4 *)(tiles + p.off_chunks);
-        k_step_spans<<<p.S, 64, 0, st>>>(desc, p.n_groups, p.LP, p.CH_STRIDE, table);
-        k_build_chunks<<<1, 256, sizeof(int) * 2 * p.S, st>>>(
-            table, p.S, p.CC, p.SMAX, p.cv || (p.p1 && !p.shared) ? p.Cin - p.CC : INT_MAX, (int *)(tiles + offsetof(TileHeader, n_chunks)), flag);
-        k_desc16<<<grid_for((size_t)p.n_groups * p.LP), 256, 0, st>>>(
-            desc, table, (const int *)(tiles + offsetof(TileHeader, n_chunks)), p.n_groups, p.LP,
-            p.CH_STRIDE, p.cv || p.p1, (uint16_t *)(tiles + p.off_desc16), flag);
-    }
-    if (p.n_g_pad > p.n_groups) {
-        // offsets of the padding groups of the last m-block: 0 (a valid patch position)
-        const size_t nd = (size_t)(p.n_g_pad - p.n_groups) * p.LP;
-        k_fill<uint16_t><<<grid_for(nd), 256, 0, st>>>(
-            (uint16_t *)(tiles + p.off_desc16) + (size_t)p.n_groups * p.LP, nd, (uint16_t)0);
+        k_desc16_abs<<<grid_for((size_t)p.n_g_pad * p.LP), 256, 0, st>>>(
+            desc, p.n_groups * p.LP, p.n_g_pad * p.LP, (uint16_t *)(tiles + p.off_desc16), flag);
+    } else if (!identity) {
+        const ChunkArgs ca{desc, p.n_groups, p.n_g_pad, p.LP, p.S, p.CH_STRIDE, p.CC, p.SMAX,
+                           p.cv || p.p1 ? p.Cin - p.CC : INT_MAX, p.cv || p.p1, (int4 *)(tiles + p.off_chunks),
+                           (int *)(tiles + offsetof(TileHeader, n_chunks)), (uint16_t *)(tiles + p.off_desc16), flag};
+        if ((int64_t)p.n_g_pad * p.LP <= kOneWorkgroupEntries && p.S <= 1024) {
+            k_chunks<<<1, 1024, sizeof(int) * 3 * p.S, st>>>(ca);
+        } else {
+            k_step_spans<<<p.S, 64, 0, st>>>(ca);
+            k_build_chunks<<<1, 256, sizeof(int) * 2 * p.S, st>>>(ca);
+            k_desc16<<<p.S, 256, 0, st>>>(ca);
+        }
     }
     if (hipGetLastError() != hipSuccess) return BSP_EDEVICE;
     if (hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
