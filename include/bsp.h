@@ -20,7 +20,7 @@
  *  - Pointers named w, mask, values, indices, rowptr, dev_tiles, x, y, bias
  *    are DEVICE pointers owned by the caller.  The library keeps no results
  *    between calls; each thread keeps the launch plans of the layers it called
- *    last (about 90 KB of host memory, freed with the thread), and some calls
+ *    last (about 130 KB of host memory, freed with the thread), and some calls
  *    keep device memory as stated at them.
  *  - `stream` is a hipStream_t passed as void* (NULL = legacy default stream).
  *    Calls are asynchronous on it unless stated otherwise.

@@ -75,6 +75,57 @@ __device__ __forceinline__ uint32_t lane_below(uint32_t v) {
 __device__ __forceinline__ uint32_t lane_above(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, true);   // wave_shl:1
 }
+// Stores a run of SP 4-pixel groups of one filter, k_cv's and k_p1's: o rounded to bf16, or fp32
+// from element `at` on.  ybase, nval: element offset of each group in filter 0 and its valid
+// pixels; yrow: offset of the filter; whole: the groups are whole and contiguous in memory.
+template <int SP>
+__device__ __forceinline__ void store_run(void *yv, bool bf16, int64_t at, const float (&o)[SP][4], const int *ybase,
+                                          const int *nval, int yrow, bool whole) {
+    if (bf16) {
+        uint32_t w[SP][2];
+#pragma unroll
+        for (int t = 0; t < SP; ++t) {
+            w[t][0] = pk_bf16(o[t][0], o[t][1]);
+            w[t][1] = pk_bf16(o[t][2], o[t][3]);
+        }
+        if (whole) {
+            uint16_t *y = (uint16_t *)yv + (uint32_t)(ybase[0] + yrow);
+#pragma unroll
+            for (int t = 0; t < SP; t += 2) {
+                const Raw<4> v = {{w[t][0], w[t][1], w[t + 1][0], w[t + 1][1]}};
+                *(Raw<4> *)(y + 4 * t) = v;
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < SP; ++t) {
+                uint16_t *y = (uint16_t *)yv + (uint32_t)(ybase[t] + yrow);
+                if (nval[t] == 4) {
+                    const Raw<2> v = {{w[t][0], w[t][1]}};
+                    *(Raw<2> *)y = v;
+                } else {
+                    if (nval[t] > 0) y[0] = (uint16_t)w[t][0];
+                    if (nval[t] > 1) y[1] = (uint16_t)(w[t][0] >> 16);
+                    if (nval[t] > 2) y[2] = (uint16_t)w[t][1];
+                }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < SP; ++t) {
+            float *y = (float *)yv + at + (uint32_t)(ybase[t] + yrow);
+            if (nval[t] == 4) {
+                struct __attribute__((packed, aligned(4))) F4 { float f[4]; };
+                const F4 v = {{o[t][0], o[t][1], o[t][2], o[t][3]}};
+                *(F4 *)y = v;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (i < nval[t]) y[i] = o[t][i];
+            }
+        }
+    }
+}
+
 // All ones when bit i of v is set, else 0.
 __device__ __forceinline__ uint32_t bit_mask(uint32_t v, int i) { return (uint32_t)__builtin_amdgcn_sbfe((int)v, i, 1); }
 __device__ __forceinline__ uint32_t half_mask(uint32_t v, int i) {   // halves by bits i and i + 1
@@ -103,7 +154,6 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
     const const_int *table = (const const_int *)(a.tiles + a.off_chunks);
     const unsigned char *A_g = a.tiles + a.off_a;
     const uint32_t *desc = (const uint32_t *)(a.tiles + a.off_desc16);
-    const unsigned char *zero = a.tiles + kZeroOffset;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int wp = wave & ((1 << a.lg_wp) - 1), wm = wave >> a.lg_wp;
@@ -368,51 +418,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
             for (int t = 0; t < SP; ++t)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) o[t][i] = ok ? epi(acc[m][r * SP + t][i], bv, a.relu) : qnan;
-            if (a.out_bf16) {
-                uint32_t w[SP][2];
-#pragma unroll
-                for (int t = 0; t < SP; ++t) {
-                    w[t][0] = pk_bf16(o[t][0], o[t][1]);
-                    w[t][1] = pk_bf16(o[t][2], o[t][3]);
-                }
-                if (whole[r]) {
-                    uint16_t *y = (uint16_t *)a.y + (uint32_t)(ybase[r * SP] + yrow);
-#pragma unroll
-                    for (int t = 0; t < SP; t += 2) {
-                        const Raw<4> v = {{w[t][0], w[t][1], w[t + 1][0], w[t + 1][1]}};
-                        *(Raw<4> *)(y + 4 * t) = v;
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < SP; ++t) {
-                        const int nv = nval[r * SP + t];
-                        uint16_t *y = (uint16_t *)a.y + (uint32_t)(ybase[r * SP + t] + yrow);
-                        if (nv == 4) {
-                            const Raw<2> v = {{w[t][0], w[t][1]}};
-                            *(Raw<2> *)y = v;
-                        } else {
-                            if (nv > 0) y[0] = (uint16_t)w[t][0];
-                            if (nv > 1) y[1] = (uint16_t)(w[t][0] >> 16);
-                            if (nv > 2) y[2] = (uint16_t)w[t][1];
-                        }
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int t = 0; t < SP; ++t) {
-                    const int nv = nval[r * SP + t];
-                    float *y = (float *)a.y + (uint32_t)(ybase[r * SP + t] + yrow);
-                    if (nv == 4) {
-                        struct __attribute__((packed, aligned(4))) F4 { float f[4]; };
-                        const F4 v = {{o[t][0], o[t][1], o[t][2], o[t][3]}};
-                        *(F4 *)y = v;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i)
-                            if (i < nv) y[i] = o[t][i];
-                    }
-                }
-            }
+            store_run<SP>(a.y, a.out_bf16, 0, o, ybase + r * SP, nval + r * SP, yrow, whole[r]);
         }
     }
 }

@@ -38,7 +38,6 @@ using cv::Raw;
 using cv::s16x4;
 using fwd::epi;
 using fwd::lds_addr;
-using fwd::pk_bf16;
 using fwd::uni;
 
 template <int SW, int TM, int TPG, int NT, bool MAP, bool IDENT>
@@ -248,51 +247,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_p1(P1Args a) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         o[t][i] = !ok ? qnan : part ? acc[m][r * SP + t][i] : epi(acc[m][r * SP + t][i], bv, a.relu);
-                if (a.out_bf16 && !part) {
-                    uint32_t w[SP][2];
-#pragma unroll
-                    for (int t = 0; t < SP; ++t) {
-                        w[t][0] = pk_bf16(o[t][0], o[t][1]);
-                        w[t][1] = pk_bf16(o[t][2], o[t][3]);
-                    }
-                    if (whole[r]) {
-                        uint16_t *y = (uint16_t *)a.y + (uint32_t)(ybase[r * SP] + yrow);
-#pragma unroll
-                        for (int t = 0; t < SP; t += 2) {
-                            const Raw<4> v = {{w[t][0], w[t][1], w[t + 1][0], w[t + 1][1]}};
-                            *(Raw<4> *)(y + 4 * t) = v;
-                        }
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < SP; ++t) {
-                            const int nv = nval[r * SP + t];
-                            uint16_t *y = (uint16_t *)a.y + (uint32_t)(ybase[r * SP + t] + yrow);
-                            if (nv == 4) {
-                                const Raw<2> v = {{w[t][0], w[t][1]}};
-                                *(Raw<2> *)y = v;
-                            } else {
-                                if (nv > 0) y[0] = (uint16_t)w[t][0];
-                                if (nv > 1) y[1] = (uint16_t)(w[t][0] >> 16);
-                                if (nv > 2) y[2] = (uint16_t)w[t][1];
-                            }
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < SP; ++t) {
-                        const int nv = nval[r * SP + t];
-                        float *y = (float *)a.y + pbase + (uint32_t)(ybase[r * SP + t] + yrow);
-                        if (nv == 4) {
-                            struct __attribute__((packed, aligned(4))) F4 { float f[4]; };
-                            const F4 v = {{o[t][0], o[t][1], o[t][2], o[t][3]}};
-                            *(F4 *)y = v;
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < 3; ++i)
-                                if (i < nv) y[i] = o[t][i];
-                        }
-                    }
-                }
+                cv::store_run<SP>(a.y, a.out_bf16 && !part, pbase, o, ybase + r * SP, nval + r * SP, yrow, whole[r]);
             }
         }
     };

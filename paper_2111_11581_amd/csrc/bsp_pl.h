@@ -39,17 +39,17 @@ using namespace bsp::fwd;
 
 constexpr int kPlThreads = 512;
 
-// MODE 1: stride 1, a granule holds two 4-pixel groups.
+// A granule holds two 4-pixel groups.
 // G: list groups of an m-block (0: the identity list).  With G > 1 the m-block's MT
 // m-tiles are G whole groups of MT / G m-tiles; with G = 1 the m-block lies inside one
 // group.  A wave's TM m-tiles always lie in one group.
-template <int MODE, int NSUB, int TM, bool MAP = false, int G = 0>
+template <int NSUB, int TM, bool MAP = false, int G = 0>
 __global__ __launch_bounds__(kPlThreads, 1) void k_pl(PwArgs a) {
-    typedef Gat<uint16_t, MODE> GT;
+    typedef Gat<uint16_t, 1> GT;
     constexpr int Q = kWaves / NSUB;              // multiplying waves per sub-tile
     constexpr int MT = TM * Q;                    // m-tiles of the m-block
     constexpr int NP = 64 * NSUB;                 // output pixels of a tile
-    constexpr int RB = NP * 2 * MODE;             // patch bytes per channel
+    constexpr int RB = NP * 2;                    // patch bytes per channel
     constexpr int GPC = RB / 16;                  // granules per channel
     constexpr int GG = G == 0 ? 1 : G;            // patches per step
     constexpr int PCOPY = GG * 32 * GPC / kThreads;   // patch copies per producer wave and step
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kPlThreads, 1) void k_pl(PwArgs a) {
     // lane's 8 channels x 4 pixels of a step: channel 8 kg + j at byte j * RB, pixels of
     // group n16 of sub-tile ps, in the patch of the wave's list group
     const int glw = G > 1 ? m_loc0 / (MT / GG) : 0;
-    const int b_lane = glw * PB1 + 8 * kg * RB + (ps * kGroups + n16) * 4 * 2 * MODE;
+    const int b_lane = glw * PB1 + 8 * kg * RB + (ps * kGroups + n16) * 4 * 2;
     // weights of step j of a stage (m-tile t at + t * a_mstr)
     const int a_mstr = res ? S * 1024 : 1024;
     auto read_step = [&](const unsigned char *pb, const unsigned char *w, typename GT::Raw &r, uint4 (&ar)[TM]) {
@@ -516,20 +516,19 @@ typedef void (*pl_fn)(PwArgs);
 
 // Instantiation choice: the m-block must hold a multiple of 4 m-tiles (one weight
 // tile per copying wave and step), so with two sub-tiles a wave has 2 or 4 m-tiles.
-template <int MODE>
-pl_fn pl_pick(int NSUB, int TM, bool map) {
+inline pl_fn pl_pick(int NSUB, int TM, bool map) {
     if (NSUB == 1) {
         switch (TM) {
-            case 1: return map ? k_pl<MODE, 1, 1, true> : k_pl<MODE, 1, 1, false>;
-            case 2: return map ? k_pl<MODE, 1, 2, true> : k_pl<MODE, 1, 2, false>;
-            case 4: return map ? k_pl<MODE, 1, 4, true> : k_pl<MODE, 1, 4, false>;
+            case 1: return map ? k_pl<1, 1, true> : k_pl<1, 1, false>;
+            case 2: return map ? k_pl<1, 2, true> : k_pl<1, 2, false>;
+            case 4: return map ? k_pl<1, 4, true> : k_pl<1, 4, false>;
             default: return nullptr;
         }
     }
     if (NSUB == 2) {
         switch (TM) {
-            case 2: return map ? k_pl<MODE, 2, 2, true> : k_pl<MODE, 2, 2, false>;
-            case 4: return map ? k_pl<MODE, 2, 4, true> : k_pl<MODE, 2, 4, false>;
+            case 2: return map ? k_pl<2, 2, true> : k_pl<2, 2, false>;
+            case 4: return map ? k_pl<2, 4, true> : k_pl<2, 4, false>;
             default: return nullptr;
         }
     }
@@ -540,15 +539,15 @@ pl_fn pl_pick(int NSUB, int TM, bool map) {
 // one group, so groups of one m-tile take one m-tile per wave.
 inline pl_fn pl_pick_g(int NSUB, int TM, int G) {
     if (G == 1) {
-        if (NSUB == 1) return TM == 1 ? k_pl<1, 1, 1, false, 1> : TM == 2 ? k_pl<1, 1, 2, false, 1>
-                                      : TM == 4 ? k_pl<1, 1, 4, false, 1> : nullptr;
-        if (NSUB == 2) return TM == 2 ? k_pl<1, 2, 2, false, 1> : TM == 4 ? k_pl<1, 2, 4, false, 1> : nullptr;
+        if (NSUB == 1) return TM == 1 ? k_pl<1, 1, false, 1> : TM == 2 ? k_pl<1, 2, false, 1>
+                                      : TM == 4 ? k_pl<1, 4, false, 1> : nullptr;
+        if (NSUB == 2) return TM == 2 ? k_pl<2, 2, false, 1> : TM == 4 ? k_pl<2, 4, false, 1> : nullptr;
     }
     if (G == 2) {
-        if (NSUB == 1) return TM == 1 ? k_pl<1, 1, 1, false, 2> : TM == 2 ? k_pl<1, 1, 2, false, 2> : nullptr;
-        if (NSUB == 2) return TM == 2 ? k_pl<1, 2, 2, false, 2> : nullptr;
+        if (NSUB == 1) return TM == 1 ? k_pl<1, 1, false, 2> : TM == 2 ? k_pl<1, 2, false, 2> : nullptr;
+        if (NSUB == 2) return TM == 2 ? k_pl<2, 2, false, 2> : nullptr;
     }
-    if (G == 4 && NSUB == 1) return TM == 1 ? k_pl<1, 1, 1, false, 4> : TM == 2 ? k_pl<1, 1, 2, false, 4> : nullptr;
+    if (G == 4 && NSUB == 1) return TM == 1 ? k_pl<1, 1, false, 4> : TM == 2 ? k_pl<1, 2, false, 4> : nullptr;
     return nullptr;
 }
 

@@ -4,7 +4,7 @@
 namespace bsp {
 namespace pl {
 
-pl_fn pick_1(int NSUB, int TM, bool map) { return pl_pick<1>(NSUB, TM, map); }
+pl_fn pick_1(int NSUB, int TM, bool map) { return pl_pick(NSUB, TM, map); }
 
 }  // namespace pl
 }  // namespace bsp

@@ -243,23 +243,6 @@ static bool plan_pointwise(Plan *p, int span_req, int n_mt, int mpg, int astep) 
     return true;
 }
 
-// Tiling of a bf16 pointwise layer with one identity list for its own kernel
-// (k_pl): one workgroup of 8 waves per CU, 4 multiplying and 4 copying, an m-block of
-// MT = TM * 4 / NSUB m-tiles (a multiple of 4) and tiles of 64 NSUB pixels; stages of
-// SPS steps in NB LDS buffers.  Scored for the nominal batch with a serial model of a
-// stage: the copying waves' issue time (about 90 cycles per 1 KB copy per wave, 2.2
-// times that from input rows off 16-byte boundaries), the multiplying waves' steps
-// (4 MFMAs of 16 cycles per m-tile and about 100 cycles of gathers and LDS latency),
-// at least the copy latency spread over the stages ahead, plus a fixed cost per
-// stage (barrier, waits, loop); per tile the epilogue's stores (10 bytes per cycle);
-// never below the HBM time.  The fixed and latency costs were fitted to a GPU sweep
-// of every tiling of the ResNet-50 pointwise layers (the model's choice is within 1%
-// of the fastest tiling there), which found large stages (4 steps) with two or three
-// buffers best.
-// Per-block-row lists (column and block-punched blocks, stride 1) run with gathered
-// lists: an m-block holds G whole list groups (or lies inside one group), each step
-// stages G patches, and the m-block's lists (16-bit channels) stay in LDS; each patch
-// copy costs a list read and a multiply-add more.  Returns false when nothing fits.
 // The layout of a plan's lists as one identity list, pruned weights zero in the tiles.
 static Plan zero_expanded(const Plan &p) {
     Plan d = p;
@@ -423,6 +406,23 @@ static bool pl_g_ok(int nsub, int tm, int g) {   // instantiated (NSUB, TM, G) o
     return false;
 }
 
+// Tiling of a bf16 pointwise layer with one identity list for its own kernel
+// (k_pl): one workgroup of 8 waves per CU, 4 multiplying and 4 copying, an m-block of
+// MT = TM * 4 / NSUB m-tiles (a multiple of 4) and tiles of 64 NSUB pixels; stages of
+// SPS steps in NB LDS buffers.  Scored for the nominal batch with a serial model of a
+// stage: the copying waves' issue time (about 90 cycles per 1 KB copy per wave, 2.2
+// times that from input rows off 16-byte boundaries), the multiplying waves' steps
+// (4 MFMAs of 16 cycles per m-tile and about 100 cycles of gathers and LDS latency),
+// at least the copy latency spread over the stages ahead, plus a fixed cost per
+// stage (barrier, waits, loop); per tile the epilogue's stores (10 bytes per cycle);
+// never below the HBM time.  The fixed and latency costs were fitted to a GPU sweep
+// of every tiling of the ResNet-50 pointwise layers (the model's choice is within 1%
+// of the fastest tiling there), which found large stages (4 steps) with two or three
+// buffers best.
+// Per-block-row lists (column and block-punched blocks, stride 1) run with gathered
+// lists: an m-block holds G whole list groups (or lies inside one group), each step
+// stages G patches, and the m-block's lists (16-bit channels) stay in LDS; each patch
+// copy costs a list read and a multiply-add more.  Returns false when nothing fits.
 static bool plan_pl(Plan *p, int n_mt, int astep) {
     const bool lists = !p->shared;
     if (p->SW != 1 || (lists && (p->counts || p->Cin > 0xffff))) return false;
@@ -942,9 +942,9 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
 // per output row, which for 2x2 and 4x4 planes copies mostly padding, so such layers run
 // as a 1x1 layer over their im2col input (its columns are the GEMM form's columns).
 constexpr int kIm2colMaxPixels = 16;
-// bf16 convs with per-block-row lists and output planes of at most this many pixels that
-// k_cv does not take (kernels not 3 wide) also run over their im2col input, with the pipelined gathered-list kernel: each kept
-// column is then one contiguous input row, copied whole, where the general kernel
+// bf16 convs with per-block-row lists and output planes of at most this many pixels also run
+// over their im2col input, with the pipelined gathered-list kernel (3-wide ones by the batch):
+// each kept column is then one contiguous input row, copied whole, where the general kernel
 // re-gathers and pads every staged row of a small image.  At stride 1 the expanded
 // input of the nominal batch must stay small: measured on gfx950 with 3-wide layers on the
 // general kernel, the 8x8 VGG-16 layers (expanded input up to 19 MB) ran 25% faster this
@@ -1073,7 +1073,7 @@ static bsp_status make_plan_new(const bsp_scheme *s, const bsp_conv_shape *conv,
 }
 
 // A plan is a pure function of the values below (the batch does not enter), so a thread
-// keeps the plans of the layers it called last: kSets x kWays of them (about 90 KB, freed with
+// keeps the plans of the layers it called last: kSets x kWays of them (about 130 KB, freed with
 // the thread), the oldest of a set replaced.  Planning takes 5 to 60 us and a forward call
 // through the Python binding plans twice.  Schemes with per-block counts, whose values are
 // an array of the caller's, are planned anew each time.

@@ -1,5 +1,5 @@
 """Sizes of packed layers asked for again, by other threads and beyond the number of plans
-a thread keeps: always those of a first call.  Neighbouring layers differ in one value."""
+a thread keeps: always those of a first call."""
 
 import threading
 

@@ -16,7 +16,7 @@ def _run(name, tmp_path):
     if cxx is None:
         pytest.skip("no C++ compiler")
     exe = str(tmp_path / name)
-    subprocess.run([cxx, "-O2", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+    subprocess.run([cxx, "-O2", "-std=c++17", "-pthread", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
                     os.path.join(ROOT, "tests", "native", name + ".cpp"), os.path.join(CSRC, "bsp_plan.cpp"), "-o", exe],
                    check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
@@ -36,3 +36,8 @@ def test_windows_hold_every_step(tmp_path):
 def test_layers_packed_for_two_kernels(tmp_path):
     """Their plans agree on the tiles and each kernel gets the batches it measured faster at."""
     _run("both", tmp_path)
+
+
+def test_kept_plans_are_those_of_a_first_call(tmp_path):
+    """A thread's kept plans against fresh threads', every pair of layers that differ in one value."""
+    _run("reuse", tmp_path)
