@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         }
     };
 
-    const int edge = cv_edge(a, img0, g0 - img0 * a.Ho, img0 + kl, g1 - (img0 + kl) * a.Ho, NE);
+    const int edge = uni(cv_edge(a, img0, g0 - img0 * a.Ho, img0 + kl, g1 - (img0 + kl) * a.Ho, NE));
     // Pipeline over the chunks: the input of chunk c is loaded while chunk c - 1
     // multiplies, then its weights (waiting for the input leaves them in flight).
     int4 cp = make_int4(0, 0, 0, 0);
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
         bool safe = false;
         if (c < nch) {
             cd = fwd::chunk_at(table, c);
-            safe = cv_safe(a, edge, cd.z, NE);
+            safe = edge != 0 && cv_safe(a, edge, cd.z, NE);
             if (safe) {
 #pragma unroll
                 for (int i = 0; i < UPT; ++i) st[i] = load_safe(cd.z, u_off[i]);
