@@ -353,9 +353,9 @@ static hipError_t launch_splitk_sum(const Plan &p, const void *part, int ks, int
 //  - large planes with many channels (more than 1024 64-pixel tiles) are memory-bound, and
 //    the deeper copy pipelines of the other kernels win: 256 -> 64 at 56x56 34 us, k_p1 41;
 //    64 -> 256 at 56x56 46, 49;
-//  - large outputs: of 38 layers and batches with 8 MB of fp32 or more, k_p1 took 1.15 times the
-//    others' time (0.95 to 1.4; it stores 16 bytes of every other group at a time), of 9 in front
-//    of k_pw with 32 MB of bf16 1.03 times (1.14 at worst; below that 0.7 to 0.95);
+//  - large outputs: of 64 layers and batches with 8 MB of fp32 or more, k_p1 took 1.11 times the
+//    others' time (0.76 to 1.41; it stores 16 bytes of every other group at a time), of 20 that
+//    k_pw would run with 32 MB of bf16 1.01 times (0.81 to 1.14), of 318 with less 0.75 times;
 //  - both would split the K loop: k_p1 wins with at most half as many parts (2048 -> 1000 at
 //    64 vectors 10.1 -> 9.2, 1024 -> 256 at 14x14, 8 images 17.5 -> 13.9), else it loses (4096
 //    -> 4096 at 128 vectors 22.8, 27.7; 2048 -> 512 at 7x7, 20 images 19.6, 25.5);

@@ -351,6 +351,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
     };
 
     const int edge = uni(cv_edge(a, img0, g0 - img0 * a.Ho, img0 + kl, g1 - (img0 + kl) * a.Ho, NE));
+    const uint16_t *x0 = a.x - a.shift;   // unit offsets count from here (cv_first)
     // Pipeline over the chunks: the input of chunk c is loaded while chunk c - 1
     // multiplies, then its weights (waiting for the input leaves them in flight).
     int4 cp = make_int4(0, 0, 0, 0);
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(kCvThreads, cv_wps(TM, NT)) void k_cv(CvArgs a) {
 #pragma unroll
                 for (int i = 0; i < UPT; ++i) st[i] = load_safe(cd.z, u_off[i]);
             } else {
-                const uint16_t *xc = a.x + cv_first(a, 0, cd.z);
+                const uint16_t *xc = x0 + (int64_t)cd.z * a.x_cs;
 #pragma unroll
                 for (int i = 0; i < UPT; ++i) st[i] = load_fast(xc, u_off[i]);
             }
