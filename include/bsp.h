@@ -228,9 +228,9 @@ bsp_status bsp_to_bcs(const bsp_scheme *scheme, const int32_t *indices, const in
  * graph.
  * Layers that two kernels may run, by the batch (the 3-wide ones excepted
  * above; lists of which both pointwise kernels make a plan): the second kernel
- * does not use the workspace but buffers of the stream's own (up to 128 MiB
- * for each of 8 streams of a device, kept until the process ends), and gives
- * way to the first where there is none, as in a stream's first call inside a
+ * does not use the workspace but a buffer of the stream's own (of 64 streams
+ * and 1 GiB in all for a device, kept until the process ends), and gives way
+ * to the first where there is none, as in a stream's first call inside a
  * capture. */
 bsp_status bsp_conv2d(const bsp_scheme *scheme, const bsp_conv_shape *shape, bsp_dtype in_dt,
                       bsp_dtype out_dt, const void *x, const void *dev_tiles,

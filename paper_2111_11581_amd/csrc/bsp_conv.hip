@@ -764,11 +764,12 @@ hipError_t launch_conv_im2col(const Plan &p, const bsp_conv_shape &c, const void
 }
 
 // Buffers of launch_alt: one per stream, so that calls on different streams need no rule.  They
-// grow to at least twice their size and stay allocated (graphs may hold them): at most 2 x 64
-// MiB for each of 8 streams of a device.  Other streams, and larger needs, are refused.
+// grow to at least twice their size and stay allocated (graphs may hold them): at most 1 GiB for
+// 64 streams of a device.  Other streams, and more than 64 MiB for a call, are refused.
 namespace {
 constexpr size_t kAltMaxBytes = 64u << 20;
-constexpr int kAltStreams = 8;
+constexpr size_t kAltTotalBytes = (size_t)1 << 30;
+constexpr int kAltStreams = 64;
 struct AltBuffer {
     hipStream_t st;
     void *buf;
@@ -781,6 +782,7 @@ std::mutex alt_mu;
 // The stream's buffer of at least `bytes`, or null.  alt_mu is held.
 static void *alt_buffer(size_t bytes, hipStream_t st) {
     static AltBuffer all[64][kAltStreams];
+    static size_t total[64];
     int dev = 0;
     if (bytes > kAltMaxBytes || st == hipStreamPerThread || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
         return nullptr;
@@ -798,6 +800,7 @@ static void *alt_buffer(size_t bytes, hipStream_t st) {
         return nullptr;
     }
     const size_t size = std::min(kAltMaxBytes, std::max(std::max(bytes, 2 * b->size), (size_t)1 << 20));
+    if (total[dev] + size > kAltTotalBytes) return nullptr;
     // another thread may be capturing: the allocation is no part of that
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     void *p = nullptr;
@@ -808,6 +811,7 @@ static void *alt_buffer(size_t bytes, hipStream_t st) {
         (void)hipGetLastError();
         return nullptr;
     }
+    total[dev] += size;
     *b = AltBuffer{st, p, size, true};
     return p;
 }

@@ -122,7 +122,7 @@ def test_a_first_call_inside_a_capture_runs(B):
 
 
 def test_streams_do_not_share_a_buffer(B):
-    """Different inputs on more streams than have a buffer, all at once, several times."""
+    """Different inputs on ten streams, all at once, several times."""
     import torch
     from paper_2111_11581_amd.layers import PackedLayer
     w = torch.randn(512, 512 * 9, device="cuda").to(torch.bfloat16)
