@@ -1002,6 +1002,15 @@ static double pl_list_us(const Plan &p, int n, int y_bytes) {
            0.48e-3 * p.n_groups * p.mt_per_group * p.S + (ks > 1 ? 2.4e-6 * ks * px * p.R + 2.0 : 0.0);
 }
 
+// The k_cv plan of p's lists stored with zeros.
+static bool plan_cv_zeros(const Plan &p, Plan *d) {
+    *d = zero_expanded(p);
+    int span;
+    double step_ch;
+    list_spans(*d, &span, &step_ch);
+    return plan_cv(d, span, step_ch, d->mt_per_group, d->mt_per_group, false);
+}
+
 // 0.92: at equal modelled times the planned kernel was the faster one more often.
 bool alt_takes(const Plan &p, const Plan &alt, int n, int out_bf16) {
     const int y_bytes = out_bf16 ? 2 : 4;
@@ -1368,19 +1377,27 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
         if (plan_cv(&c, window_req, step_ch, n_mt, mpg, !bounded) &&
             (bounded || (plan_cv(&t, span_req, step_ch, n_mt, mpg, false) &&
                          cv_us(c, kNominalImages) <= 2 * cv_us(t, kNominalImages)))) {
+            // Block-rows of less than half an m-tile leave most of their tiles empty; stored with
+            // zeros, the layer does the pruned columns' work in full tiles.  Measured with 4-row
+            // blocks, lists and zeros: 256 at 56x56, 4x, 64 images 798 and 375 us; 64 at 56x56, 4x,
+            // 84 and 43, 4 images 12 and 15; 256 at 14x14 (keeps its lists) 54 and 47, 13 and 28.
+            // Hence both batches count.  Half-full tiles gain less (8-row blocks, 64 at 56x56: 54
+            // and 43, 10 and 15; 43 -> 663 at 46x43, one image, 13 and 23) and keep their lists.
+            Plan d;
+            if (2 * p->bh_eff < kMT && !p->shared && !p->counts && p->Ho * p->Wo > kIm2colListPixels &&
+                plan_cv_zeros(*p, &d) &&
+                cv_us(c, kNominalImages) * cv_us(c, 4) > 1.4 * cv_us(d, kNominalImages) * cv_us(d, 4))
+                c = d;
             *p = c;
-            finish_layout(p, n_mt, astep);
+            finish_layout(p, p->n_groups * p->mt_per_group, astep);
             return BSP_OK;
         }
         // lists without a bound that do not fit so: stored with zeros (64 images, 16-row blocks, 4x:
         // 256 at 28x28 246 us on the general kernel's lists, which refuse some masks, 110 so; 256 at
         // 14x14 49 and 48, at 8x 38 and 48; 64 at 56x56 54 and 44)
         if (!bounded && !p->counts) {
-            Plan d = zero_expanded(*p);
-            int sr;
-            double sc;
-            list_spans(d, &sr, &sc);
-            if (plan_cv(&d, sr, sc, d.mt_per_group, d.mt_per_group, false)) {
+            Plan d;
+            if (plan_cv_zeros(*p, &d)) {
                 *p = d;
                 finish_layout(p, d.mt_per_group, astep);
                 return BSP_OK;

@@ -57,6 +57,11 @@ CASES = [
     (8, 32, 46, 46, 18, 3, (1, 1), (1, 1), (16, 64), COL, 4, True, "bf16"),
     (8, 32, 46, 46, 31, 3, (1, 1), (1, 1), (16, 32), PUNCHED, 4, False, "f32"),
     (66, 32, 46, 46, 18, 3, (2, 2), (1, 1), (16, 64), PUNCHED, 4, True, "bf16"),
+    # block-rows shorter than a tile, stored with zeros
+    (2, 20, 33, 30, 62, 3, (1, 1), (1, 1), (6, 36), COL, 2, True, "bf16"),
+    (2, 24, 25, 23, 60, 3, (1, 1), (1, 1), (4, 12), COL, 4, False, "f32"),
+    (2, 24, 33, 30, 62, 3, (1, 1), (1, 1), (2, 4), PUNCHED, 4, True, "bf16"),
+    (3, 32, 46, 46, 62, 3, (2, 2), (1, 1), (2, 12), COL, 4, False, "bf16"),
 ]
 
 

@@ -41,3 +41,8 @@ def test_layers_packed_for_two_kernels(tmp_path):
 def test_kept_plans_are_those_of_a_first_call(tmp_path):
     """A thread's kept plans against fresh threads', every pair of layers that differ in one value."""
     _run("reuse", tmp_path)
+
+
+def test_lists_of_short_block_rows(tmp_path):
+    """Lists whose tiles are partly empty are stored with zeros where that measured faster."""
+    _run("short_rows", tmp_path)
