@@ -995,11 +995,12 @@ static double pl_list_us(const Plan &p, int n, int y_bytes) {
     int ks = 1;
     if (units <= 128 && p.S >= 4) ks = std::min((int)std::min<int64_t>(16, 256 / units), p.S / 2);
     const int steps = div_up(p.S, ks);
-    const int64_t wpm = ks > 1 ? n_pt : std::min<int64_t>(n_pt, div_up(256, p.n_mb));
-    const double tiles = (double)div_up64(n_pt, wpm) * div_up64(wpm * p.n_mb * ks, 256);   // a CU's, in turn
+    // workgroups as launched: each walks a run of pixel tiles of its m-block
+    const int64_t tpw = ks > 1 ? 1 : div_up64(n_pt, std::min<int64_t>(n_pt, div_up(256 * p.occ, p.n_mb)));
+    const double tiles = (double)tpw * div_up64(div_up64(n_pt, tpw) * p.n_mb * ks, 256);   // a CU's, in turn
     const double px = (double)n * (p.is_linear ? 1 : p.H * p.W);
-    return 5.3 + tiles * (0.40 * div_up(steps, p.SMAX) + 0.145 * steps * p.MBG * p.NSUB) + 0.185e-6 * px * p.R * y_bytes +
-           0.48e-3 * p.n_groups * p.mt_per_group * p.S + (ks > 1 ? 2.4e-6 * ks * px * p.R + 2.0 : 0.0);
+    return 5.1 + tiles * (0.545 * div_up(steps, p.SMAX) + 0.14 * steps * p.MBG * p.NSUB) + 0.238e-6 * px * p.R * y_bytes +
+           0.43e-3 * p.n_groups * p.mt_per_group * p.S + (ks > 1 ? 2.2e-6 * ks * px * p.R + 2.15 : 0.0);
 }
 
 // The k_cv plan of p's lists stored with zeros.
