@@ -1344,7 +1344,7 @@ static bsp_status make_plan_impl(const bsp_scheme *s, const bsp_conv_shape *conv
 
     // bf16 pointwise layers that k_p1 always runs: stride 2 over one identity list (batch 64,
     // cold cache: 256 -> 512 at 56x56 82 -> 61 us, 512 -> 1024 at 28x28 63 -> 52, 1024 -> 2048
-    // at 14x14 47 -> 45 against the strided pipelined kernel and, for the smaller planes, a
+    // at 14x14 49.5 and 50.1 against the strided pipelined kernel and, for the smaller planes, a
     // subsampled copy), and per-block-row lists that keep at least a quarter of the columns.
     // k_p1 stages every channel a list's steps span, k_pl only the kept ones: at 4x 256 ->
     // 1024 at 14x14 23.5 -> 18.5 us and 768 -> 3072 at 256 vectors 15.7 -> 8.0 us, at 8x

@@ -45,7 +45,7 @@ int main() {
     check(516, 7, 10, 163, 3, 2, BSP_PUNCHED, 64, 16, 2, 256, 1);   // 26 and 12
     check(454, 25, 25, 24, 1, 1, BSP_COL, 64, 64, 4, 1, 64);     // 24 and 11 at 64
     check(214, 63, 63, 41, 1, 1, BSP_COL, 32, 32, 2, 1, 64);     // 68 and 32
-    check(512, 62, 58, 287, 1, 1, BSP_COL, 16, 32, 4, 1, 16);    // 76 and 44 at 16 (fp32 output), 259 workgroups planned, 250 launched
+    check(512, 62, 58, 287, 1, 1, BSP_COL, 16, 32, 4, 1, 16);    // 76 and 44 at 16
     check(3960, 0, 0, 424, 0, 1, BSP_COL, 64, 32, 4, 1, 554);    // 17 and 12 at 554 vectors
     printf("%d faults\n", bad);
     return bad;
