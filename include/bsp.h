@@ -228,10 +228,10 @@ bsp_status bsp_to_bcs(const bsp_scheme *scheme, const int32_t *indices, const in
  * graph.
  * Layers that two kernels may run, by the batch (the 3-wide ones excepted
  * above; lists of which both pointwise kernels make a plan): the second kernel
- * does not use the workspace but a buffer of the stream's own (of 64 streams
- * and 1 GiB in all for a device, kept until the process ends), and gives way
- * to the first where there is none, as in a stream's first call inside a
- * capture. */
+ * does not use the workspace but a buffer of the stream's own, in a capture
+ * of the captured stream's own (of 64 streams, 64 captured ones and 1 GiB in
+ * all for a device, kept until the process ends), and gives way to the first
+ * where there is none.  Two executables of one graph must not overlap. */
 bsp_status bsp_conv2d(const bsp_scheme *scheme, const bsp_conv_shape *shape, bsp_dtype in_dt,
                       bsp_dtype out_dt, const void *x, const void *dev_tiles,
                       const float *bias_or_null, int32_t relu, void *y, void *stream);

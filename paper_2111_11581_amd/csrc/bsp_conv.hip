@@ -763,15 +763,19 @@ hipError_t launch_conv_im2col(const Plan &p, const bsp_conv_shape &c, const void
     return launch_conv(p, c.n, ws, tiles, bias, relu, out_bf16, y, st, part);
 }
 
-// Buffers of launch_alt: one per stream, so that calls on different streams need no rule.  They
-// grow to at least twice their size and stay allocated (graphs may hold them): at most 1 GiB for
-// 64 streams of a device.  Other streams, and more than 64 MiB for a call, are refused.
+// Buffers of launch_alt: one per stream, so that calls on different streams need no rule, and one
+// per stream of each capture, as a graph may be replayed on any stream, beside other graphs of the
+// stream that it was captured on.  They grow to at least twice their size and stay allocated
+// (graphs may hold them): at most 1 GiB for 64 streams and 64 captured ones of a device.  Others,
+// and more than 64 MiB for a call, are refused.
 namespace {
 constexpr size_t kAltMaxBytes = 64u << 20;
 constexpr size_t kAltTotalBytes = (size_t)1 << 30;
 constexpr int kAltStreams = 64;
 struct AltBuffer {
     hipStream_t st;
+    unsigned long long capture;   // its id when `captured`
+    bool captured;
     void *buf;
     size_t size;
     bool used;
@@ -781,27 +785,29 @@ std::mutex alt_mu;
 
 // The stream's buffer of at least `bytes`, or null.  alt_mu is held.
 static void *alt_buffer(size_t bytes, hipStream_t st) {
-    static AltBuffer all[64][kAltStreams];
+    static AltBuffer all[64][2][kAltStreams];   // of a device, outside and inside captures
     static size_t total[64];
     int dev = 0;
     if (bytes > kAltMaxBytes || st == hipStreamPerThread || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
         return nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(st, &cap, &id) != hipSuccess || cap == hipStreamCaptureStatusInvalidated) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const bool captured = cap == hipStreamCaptureStatusActive;
     AltBuffer *b = nullptr;
-    for (AltBuffer &e : all[dev])
-        if (e.used ? e.st == st : !b) {
+    for (AltBuffer &e : all[dev][captured])
+        if (e.used ? e.st == st && (!captured || e.capture == id) : !b) {
             b = &e;
             if (e.used) break;
         }
     if (!b) return nullptr;
     if (b->used && b->size >= bytes) return b->buf;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
     const size_t size = std::min(kAltMaxBytes, std::max(std::max(bytes, 2 * b->size), (size_t)1 << 20));
     if (total[dev] + size > kAltTotalBytes) return nullptr;
-    // another thread may be capturing: the allocation is no part of that
+    // this thread or another may be capturing: the allocation is no part of that
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     void *p = nullptr;
     const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
@@ -812,7 +818,7 @@ static void *alt_buffer(size_t bytes, hipStream_t st) {
         return nullptr;
     }
     total[dev] += size;
-    *b = AltBuffer{st, p, size, true};
+    *b = AltBuffer{st, id, captured, p, size, true};
     return p;
 }
 

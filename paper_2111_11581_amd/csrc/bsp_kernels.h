@@ -46,8 +46,8 @@ hipError_t launch_stem(const Plan &p, int n, const void *x, const uint8_t *tiles
 size_t pw_part_bytes(const Plan &p, int n);
 
 // As launch_conv for the other plan of a layer's tiles (Plan::alt; c: the conv, or null for a
-// linear layer).  False, with nothing launched, when the buffer that it needs cannot be had (the
-// stream's first such call inside a capture, more than 64 MiB, out of memory).
+// linear layer).  False, with nothing launched, when the buffer that it needs cannot be had (more
+// streams or captures than there are buffers, more than 64 MiB, out of memory).
 bool launch_alt(const Plan &alt, const bsp_conv_shape *c, int n, const void *x, const uint8_t *tiles, const float *bias,
                 int relu, int out_bf16, void *y, hipStream_t st, hipError_t *e);
 

@@ -1,8 +1,7 @@
 """Layers whose tiles are packed for two kernels, at batches that either of them runs (which
 does is fixed on the host by tests/native/both.cpp): both outputs match the fp64 oracle, tiles
-of another plan give NaN on both routes, calls on several streams at once do not disturb each
-other, and inside a graph capture, where the buffer of one of them cannot be allocated, the
-other runs."""
+of another plan give NaN on both routes, and calls on several streams and graphs replayed at
+once do not disturb each other."""
 
 from __future__ import annotations
 
@@ -142,3 +141,41 @@ def test_streams_do_not_share_a_buffer(B):
     for y, ref, bound in zip(ys, refs, bounds):
         for r in range(5):
             assert torch.all((y[r] - ref).abs() <= bound)
+
+
+def test_graphs_of_one_stream_do_not_share_a_buffer(B):
+    """Graphs captured one after the other on a stream that has run the layer, replayed on
+    streams of their own while that stream runs it again: every output as in an eager call
+    alone, bit for bit (so the captured calls take the same kernel)."""
+    import torch
+    from paper_2111_11581_amd.layers import PackedLayer
+    w = torch.randn(512, 512 * 9, device="cuda").to(torch.bfloat16)
+    layer = PackedLayer(B.Scheme(512, 512 * 9, 0, 0, B.DENSE, 1, 1), B.BF16, w, conv=B.ConvShape(4, 512, 4, 4, 3, 3, 1, 1, 1, 1))
+    n_graphs = 4
+    xs = [torch.randn(4, 512, 4, 4, device="cuda").to(torch.bfloat16) for _ in range(n_graphs + 1)]
+    refs = [torch.empty(4, 512, 4, 4, device="cuda") for _ in xs]
+    ys = [torch.empty(4, 512, 4, 4, device="cuda") for _ in xs]
+    main = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for x, ref in zip(xs, refs):
+        layer.conv2d(x, ref, 4, B.F32, stream=main)
+        torch.cuda.synchronize()
+    graphs = []
+    for i in range(n_graphs):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=main):
+            layer.conv2d(xs[i], ys[i], 4, B.F32, stream=main)
+        graphs.append(g)
+    streams = [torch.cuda.Stream() for _ in range(n_graphs)]
+    for _ in range(3):
+        for y in ys:
+            y.fill_(7.0)
+        torch.cuda.synchronize()
+        for _ in range(10):
+            for g, s in zip(graphs, streams):
+                with torch.cuda.stream(s):
+                    g.replay()
+            layer.conv2d(xs[-1], ys[-1], 4, B.F32, stream=main)
+        torch.cuda.synchronize()
+        for y, ref in zip(ys, refs):
+            assert torch.equal(y, ref)
